@@ -101,6 +101,44 @@ static void check_ptr(const void* p, const char* what) {
     if (!p) throw Error{NS_E_INVALID, std::string("null pointer: ") + what};
 }
 
+// Weights that digits of a common scale hold as well as doubles do: within
+// every block of 512 inputs of a unit, and of 512 units of an input (the
+// adjoint's rows), the largest weight is at most 8 times the root mean square.
+// The digits' error goes with the largest weight and the FP64 product's with
+// the root mean square; for normal draws the former (largest / rms about 3.5)
+// is half the latter, so at 8 they are about equal.
+static bool digit_weights_even(const ns_net_desc& nd) {
+    constexpr int BLOCK = 512;
+    auto even = [](double mx, double ss, int n) {
+        return mx * mx * n <= 64.0 * ss && (mx == 0.0 || (mx > 1e-140 && mx < 1e140));
+    };
+    for (int l = 1; l < nd.n_layers; ++l) {
+        const int K = nd.dims[l], N = nd.dims[l + 1];
+        std::vector<double> cm(K, 0.0), cs(K, 0.0);
+        for (int n = 0; n < N; ++n) {
+            for (int k0 = 0; k0 < K; k0 += BLOCK) {
+                double mx = 0.0, ss = 0.0;
+                for (int k = k0; k < std::min(K, k0 + BLOCK); ++k) {
+                    const double v = std::fabs(nd.W[l][(size_t)n * K + k]);
+                    if (!std::isfinite(v)) return false;
+                    mx = std::max(mx, v);
+                    ss += v * v;
+                    cm[k] = std::max(cm[k], v);
+                    cs[k] += v * v;
+                }
+                if (!even(mx, ss, std::min(BLOCK, K - k0))) return false;
+            }
+            if ((n + 1) % BLOCK == 0 || n + 1 == N) {
+                for (int k = 0; k < K; ++k) {
+                    if (!even(cm[k], cs[k], n % BLOCK + 1)) return false;
+                    cm[k] = cs[k] = 0.0;
+                }
+            }
+        }
+    }
+    return true;
+}
+
 static Net* build_net(const ns_net_desc& nd, int mu_rows) {
     NS_CHECK(nd.n_layers >= 2, NS_E_SHAPE, "emulator needs >= 2 layers");
     check_ptr(nd.dims, "net.dims");
@@ -210,6 +248,14 @@ static Net* build_net(const ns_net_desc& nd, int mu_rows) {
                 upload(ly->gamma32, ga.data(), (size_t)N);
             }
         }
+        net->digits = digit_shape(net->dims) && digit_weights_even(nd);
+        if (net->digits)
+            for (int l = 1; l < nd.n_layers; ++l) {
+                Layer* ly = net->layers[l];
+                digit_weights(ly->W64, ly->n_out, ly->n_in, ly->Wd, ly->wback);
+                digit_weights(ly->WT64, ly->n_in, ly->n_pad, ly->WTd, ly->wtback);
+            }
+        if (net->digits) NS_HIP(hipStreamSynchronize(nullptr));   // calls may come on any stream
         net->narrow64 = narrow_f64_shape(net->dims);
         if (net->narrow64) {
             std::vector<double> f64;

@@ -18,6 +18,7 @@
 // blockIdx.z selecting the network, so a 4096-walker layer fills the chip.
 #include "devutil.h"
 #include "gemm_bf16.h"
+#include "gemm_i8.h"
 #include "nsmi.h"
 
 namespace nsmi {
@@ -136,6 +137,13 @@ template <class T, class OutT> struct EpiHidden {
     T* tsave = nullptr;
     struct Col { T b, be, ga; };
     __device__ __forceinline__ Col col(int c) const { return Col{b[c], beta[c], gamma[c]}; }
+    // pre: what an output takes besides its column's parameters, for kernels
+    // that load it ahead of the product; period: rows after which it repeats
+    // (0: it does not), zr: the row modulo that
+    struct Pre {};
+    __device__ __forceinline__ int period() const { return 0; }
+    __device__ __forceinline__ Pre pre(int64_t, int, int) const { return Pre{}; }
+    __device__ __forceinline__ void store(int64_t r, int c, const Col& p, T acc, Pre) const { store(r, c, p, acc); }
     __device__ __forceinline__ void store(int64_t r, int c, const Col& p, T acc) const {
         const T t = acc + p.b;
         if (tsave) tsave[r * ldo + c] = t;
@@ -150,8 +158,14 @@ template <class T> struct EpiBack {
     T* out; int64_t ldo;
     struct Col { T be, ga; };
     __device__ __forceinline__ Col col(int c) const { return Col{beta[c], gamma[c]}; }
+    struct Pre { T t; };
+    __device__ __forceinline__ int period() const { return 0; }
+    __device__ __forceinline__ Pre pre(int64_t r, int c, int) const { return Pre{tsave[r * ldo + c]}; }
     __device__ __forceinline__ void store(int64_t r, int c, const Col& p, T acc) const {
-        const T t = tsave[r * ldo + c];
+        store(r, c, p, acc, pre(r, c, 0));
+    }
+    __device__ __forceinline__ void store(int64_t r, int c, const Col& p, T acc, Pre q) const {
+        const T t = q.t;
         const T s = sigmoid<T>(p.be * t);
         out[r * ldo + c] = acc * (p.ga + (T(1) - p.ga) * (s + p.be * t * s * (T(1) - s)));
     }
@@ -171,8 +185,14 @@ template <class T> struct EpiOut {
     T* out; int64_t ldo; int mu_rows; int n_out; int is_log;
     struct Col { T b, s, mu0; int c; };
     __device__ __forceinline__ Col col(int c) const { return Col{b[c], sigma[c], mu[c], c}; }
+    struct Pre { T m; };
+    __device__ __forceinline__ int period() const { return mu_rows > 1 ? mu_rows : 0; }
+    __device__ __forceinline__ Pre pre(int64_t, int c, int zr) const { return Pre{mu[(int64_t)zr * n_out + c]}; }
     __device__ __forceinline__ void store(int64_t r, int c, const Col& p, T acc) const {
-        const T m = mu_rows > 1 ? mu[(int64_t)(r % mu_rows) * n_out + c] : p.mu0;
+        store(r, c, p, acc, Pre{mu_rows > 1 ? mu[(int64_t)(r % mu_rows) * n_out + c] : p.mu0});
+    }
+    __device__ __forceinline__ void store(int64_t r, int c, const Col& p, T acc, Pre q) const {
+        const T m = q.m;
         T y = m + p.s * (acc + p.b);
         if (is_log) y = exp10_of<T>(y);
         out[r * ldo + c] = y;
@@ -537,6 +557,102 @@ __global__ __launch_bounds__(256, 4) void gemm_f64_kernel(Group<Epi> G, int64_t 
     }
 }
 
+// ------------------------------------------------- FP64 on the int8 pipe
+// Digit tiles and factors of W [N x K] (K a multiple of 32): one wave per
+// (unit, block of DG_K inputs), a lane eight inputs; units past N are zeros.
+__global__ __launch_bounds__(64) void digit_weights_kernel(const double* __restrict__ W, int N, int K,
+                                                           char* __restrict__ tiles, double* __restrict__ back) {
+    const int n = blockIdx.x, blk = blockIdx.y, lane = threadIdx.x;
+    const int k = blk * DG_K + lane * 8;
+    double x[8];
+    int h = 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        x[e] = n < N && k < K ? W[(int64_t)n * K + k + e] : 0.0;
+        h = max(h, __double2hiint(x[e]) & 0x7fffffff);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) h = max(h, __shfl_xor(h, o, 64));
+    const DigitScale sc = digit_scale(h);
+    if (lane == 0) back[(int64_t)blk * gridDim.x + n] = sc.back;
+    if (k >= K) return;
+    uint32_t a[DG_N], c[DG_N];
+    const double x0[4] = {x[0], x[1], x[2], x[3]}, x1[4] = {x[4], x[5], x[6], x[7]};
+    pack4(x0, sc.to_int, a);
+    pack4(x1, sc.to_int, c);
+    char* t = tiles + digit_offset(n, k, K);
+#pragma unroll
+    for (int i = 0; i < DG_N; ++i) *reinterpret_cast<uint2*>(t + i * 1024) = make_uint2(a[i], c[i]);
+}
+
+bool digit_shape(const std::vector<int>& dims) {
+    const int L = (int)dims.size() - 1;
+    if (L < 2) return false;
+    for (int l = 1; l < L; ++l)
+        if (dims[l] < 256) return false;
+    return true;
+}
+
+void digit_weights(const DevBuf& W64, int N, int K, DevBuf& tiles, DevBuf& back) {
+    const int n32 = (N + 31) / 32 * 32, blocks = (K + DG_K - 1) / DG_K;
+    tiles.ensure((size_t)n32 * K * DG_N);
+    back.ensure((size_t)n32 * blocks * sizeof(double));
+    hipLaunchKernelGGL(digit_weights_kernel, dim3((unsigned)n32, (unsigned)blocks), dim3(64), 0, nullptr,
+                       W64.as<double>(), N, K, tiles.as<char>(), back.as<double>());
+    NS_HIP(hipGetLastError());
+}
+
+// One layer of G networks on digits: the rows' fragments (into the model's
+// workspace), then the products.
+template <class Epi>
+static void launch_gemm_i8(ns_model* m, const Group<Epi>& P, int64_t rows, int N, int K, int G, const int* count,
+                           int rpw, hipStream_t s) {
+    const int64_t nb = (N + 31) / 32, rb = (rows + DG_ROWS - 1) / DG_ROWS, m32 = rb * DG_ROWS;
+    const int blocks = (K + DG_K - 1) / DG_K;
+    const size_t tile_bytes = (size_t)m32 * K * DG_N, back_bytes = (size_t)m32 * blocks * sizeof(double);
+    m->ws_digits.ensure(G * (tile_bytes + back_bytes));
+    DigitRows R{};
+    DigitGroup<Epi> D{};
+    for (int g = 0; g < G; ++g) {
+        R.A[g] = static_cast<const double*>(P.A[g]);
+        R.tiles[g] = m->ws_digits.as<char>() + g * tile_bytes;
+        R.back[g] = reinterpret_cast<double*>(m->ws_digits.as<char>() + G * tile_bytes + g * back_bytes);
+        D.A[g] = R.tiles[g];
+        D.Al[g] = R.back[g];
+        D.W[g] = P.W[g];
+        D.Wl[g] = static_cast<const double*>(P.Wl[g]);
+        D.epi[g] = P.epi[g];
+    }
+    hipLaunchKernelGGL(digit_rows_kernel<0>, dim3((unsigned)((rows + 3) / 4), (unsigned)blocks, (unsigned)G), dim3(256),
+                       0, s, R, (int64_t)K, rows, K, m32, count, rpw);
+    const bool multi = K > DG_K;
+    const int64_t cus = device_cus(m->device), groups = rb * G;
+    auto rounds = [&](int64_t per_row_block) { return (groups * per_row_block + cus - 1) / cus; };
+    // tiles per workgroup that give one round over the CUs where the batch
+    // allows it, in units of the `step` tiles that run side by side
+    auto per_wg = [&](int step, int64_t most) {
+        const int64_t sets = (nb + step - 1) / step;
+        return step * std::min<int64_t>({(groups * sets + cus - 1) / cus, sets, most});
+    };
+    // thousands of cycles of each form (shader clock, one network of 2 500
+    // outputs at 60 to 4 096 rows): a split tile costs 10 with its sum and
+    // barrier; a wave's own tile 14, 29 where two waves share a SIMD, plus 12
+    // for the copy and the first epilogue
+    const int64_t t8 = per_wg(1, multi ? GI_TPW : nb), t4 = per_wg(4, multi ? 1 : nb), t1 = per_wg(8, multi ? 1 : nb);
+    const int64_t c8 = rounds((nb + t8 - 1) / t8) * (4 + 10 * t8);
+    const int64_t c4 = rounds((nb + t4 - 1) / t4) * (12 + 18 * t4 / 4);
+    const int64_t c1 = rounds((nb + t1 - 1) / t1) * (12 + 32 * t1 / 8);
+    auto go = [&](auto kern, int64_t tpw, int waves, int bytes) {
+        if (bytes && m->lds_attr_set.insert((const void*)kern).second)
+            NS_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+        const dim3 grid((unsigned)((nb + tpw - 1) / tpw), (unsigned)rb, (unsigned)G);
+        hipLaunchKernelGGL(kern, grid, dim3(64 * waves), bytes, s, D, m32, rows, N, K, (int)tpw, count, rpw);
+    };
+    if (c8 <= c4 && c8 <= c1) go(multi ? gemm_i8_kernel<Epi, true> : gemm_i8_kernel<Epi, false>, t8, 8, 0);
+    else if (c4 <= c1) go(multi ? gemm_i8_wide_kernel<Epi, 4, true> : gemm_i8_wide_kernel<Epi, 4, false>, t4, 4, GW_LDS_BYTES);
+    else go(multi ? gemm_i8_wide_kernel<Epi, 8, true> : gemm_i8_wide_kernel<Epi, 8, false>, t1, 8, GW_LDS_BYTES);
+}
+
 // ------------------------------------------------------ BF16 tile autotuner
 // Candidate tile configurations of gemm_bf16_t.  All of them accumulate each
 // output over K in the same order, so the choice never changes a result; the
@@ -720,8 +836,6 @@ void emulator_forward(ns_model* m, const int* nets, int G, const double* theta, 
     size_t max_w = 0;
     for (int l = 1; l < L; ++l) max_w = std::max(max_w, (size_t)net0.dims[l]);
     const size_t act_stride = (size_t)rows * max_w;      // elements per network
-    m->ws_act[0].ensure(G * act_stride * act_elem);
-    m->ws_act[1].ensure(G * act_stride * act_elem);
     // pre-activation saves for the adjoint: slot (g, l-1) holds t of hidden layer l
     const size_t tsz = prec == NS_FP64 ? 8 : 4;
     const size_t save_stride = (size_t)(L - 1) * act_stride;   // elements per network
@@ -730,6 +844,11 @@ void emulator_forward(ns_model* m, const int* nets, int G, const double* theta, 
     auto tslot = [&](int g, int slot) -> void* {
         return tbase ? (void*)(tbase + ((size_t)g * save_stride + (size_t)slot * act_stride) * tsz) : nullptr;
     };
+    if (prec == NS_FP64 && emulator_forward_digits(m, nets, G, theta, ld, B, outs, ldo, is_log, (double*)tbase,
+                                                   save_stride, act_stride, count, s))
+        return;
+    m->ws_act[0].ensure(G * act_stride * act_elem);
+    m->ws_act[1].ensure(G * act_stride * act_elem);
     {
         TraceScope ts(m, s, "emu_first_layer");
         if (prec == NS_FP64)
@@ -760,21 +879,27 @@ void emulator_forward(ns_model* m, const int* nets, int G, const double* theta, 
                 Group<EpiHidden<double, double>> P{};
                 for (int g = 0; g < G; ++g) {
                     const Layer& ly = *m->nets[nets[g]]->layers[l];
-                    P.A[g] = A_of(g); P.W[g] = ly.W64.p;
+                    P.A[g] = A_of(g); P.W[g] = net0.digits ? ly.Wd.p : ly.W64.p; P.Wl[g] = ly.wback.p;
                     P.epi[g] = {ly.b64.as<double>(), ly.beta64.as<double>(), ly.gamma64.as<double>(),
                                 (double*)D_of(g), (int64_t)N, (double*)tslot(g, l)};
                 }
-                launch_gemm_f64(m, P, (int64_t)K, rows, N, K, G, count, rpw, s);
+                if (net0.digits)
+                    launch_gemm_i8(m, P, rows, N, K, G, count, rpw, s);
+                else
+                    launch_gemm_f64(m, P, (int64_t)K, rows, N, K, G, count, rpw, s);
             } else {
                 Group<EpiOut<double>> P{};
                 for (int g = 0; g < G; ++g) {
                     const Net& net = *m->nets[nets[g]];
                     const Layer& ly = *net.layers[l];
-                    P.A[g] = A_of(g); P.W[g] = ly.W64.p;
+                    P.A[g] = A_of(g); P.W[g] = net0.digits ? ly.Wd.p : ly.W64.p; P.Wl[g] = ly.wback.p;
                     P.epi[g] = {ly.b64.as<double>(), net.out_mu64.as<double>(), net.out_sigma64.as<double>(),
                                 (double*)D_of(g), ldo, net.out_mu_rows, N, is_log[g]};
                 }
-                launch_gemm_f64(m, P, (int64_t)K, rows, N, K, G, count, rpw, s);
+                if (net0.digits)
+                    launch_gemm_i8(m, P, rows, N, K, G, count, rpw, s);
+                else
+                    launch_gemm_f64(m, P, (int64_t)K, rows, N, K, G, count, rpw, s);
             }
         } else if (prec == NS_FP32) {
             NS_CHECK(K % GF_K == 0, NS_E_UNSUPPORTED, "FP32 MFMA layers need K % 32 == 0");
@@ -897,7 +1022,13 @@ static void backward_impl(ns_model* m, const int* nets, int G, int64_t B, const 
         return (const T*)(tbase + ((size_t)g * save_stride + (size_t)slot * act_stride) * sizeof(T));
     };
     int cur = 0;
-    for (int l = L - 1; l >= 1; --l) {
+    bool done = false;
+    if constexpr (sizeof(T) == 8) {
+        done = emulator_backward_digits(m, nets, G, B, m->ws_gact[0].as<double>(), m->ws_gact[1].as<double>(), gstride,
+                                        (const double*)tbase, save_stride, act_stride, s);
+        if (done) cur = 1;
+    }
+    for (int l = L - 1; l >= 1 && !done; --l) {
         const int Kred = net0.layers[l]->n_pad, Nout = net0.dims[l];
         TraceScope ts(m, s, f64 ? "adj_gemm_f64" : "adj_gemm_f32");
         Group<EpiBack<T>> P{};
@@ -906,14 +1037,18 @@ static void backward_impl(ns_model* m, const int* nets, int G, int64_t B, const 
             const Layer& ly = *net.layers[l];
             const Layer& lb = *net.layers[l - 1];
             P.A[g] = m->ws_gact[cur].as<T>() + g * gstride;
-            P.W[g] = f64 ? ly.WT64.p : ly.WT32.p;
+            P.W[g] = f64 ? (net0.digits ? ly.WTd.p : ly.WT64.p) : ly.WT32.p;
+            P.Wl[g] = ly.wtback.p;
             P.epi[g] = {tslot(g, l - 1), (const T*)(f64 ? lb.beta64.p : lb.beta32.p),
                         (const T*)(f64 ? lb.gamma64.p : lb.gamma32.p), m->ws_gact[cur ^ 1].as<T>() + g * gstride,
                         (int64_t)Nout};
         }
-        if constexpr (sizeof(T) == 8)
-            launch_gemm_f64(m, P, (int64_t)Kred, rows, Nout, Kred, G, count, rpw, s);
-        else
+        if constexpr (sizeof(T) == 8) {
+            if (net0.digits)
+                launch_gemm_i8(m, P, rows, Nout, Kred, G, count, rpw, s);
+            else
+                launch_gemm_f64(m, P, (int64_t)Kred, rows, Nout, Kred, G, count, rpw, s);
+        } else
             hipLaunchKernelGGL((gemm_f32_kernel<EpiBack<T>>), grid3(rows, Nout, GB_M, GB_N, G), dim3(256), 0, s, P,
                                (int64_t)Kred, rows, Nout, Kred, count, rpw);
         NS_HIP(hipGetLastError());

@@ -11,6 +11,7 @@
 #include <cstddef>
 #include <cstring>
 #include <map>
+#include <set>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -85,6 +86,8 @@ struct Layer {
     DevBuf Whi, Wlo;                         // bf16 hi / lo split of W
     int n_pad = 0;                           // n_out rounded up to 64
     DevBuf WT64, WT32;                       // W^T [n_in x n_pad], zero padded (adjoint)
+    DevBuf Wd, wback, WTd, wtback;           // base-256 digit tiles of W and W^T and their units' factors
+                                             // (networks that pass digit_shape; gemm_i8.h)
 };
 
 struct Net {
@@ -109,6 +112,7 @@ struct Net {
     // (kq NT + nt) 64, lane q holding W[16 nt + q % 16][4 kq + q / 16] (0 past N)
     bool narrow64 = false;
     DevBuf Wf64;
+    bool digits = false;                     // FP64 GEMM layers run on int8 digits
     ~Net();
 };
 
@@ -169,6 +173,7 @@ struct ns_model {
 
     // workspaces (grow on demand)
     nsmi::DevBuf ws_act[2];          // hidden activations ping-pong
+    nsmi::DevBuf ws_digits;          // digit fragments of one layer's input rows, and the rows' factors
     nsmi::DevBuf ws_out;             // emulator outputs / model vectors
     nsmi::DevBuf ws_aux;             // stage outputs (spline M, spectra, ...)
     nsmi::DevBuf ws_theta;           // theta scratch for the sampler
@@ -185,6 +190,7 @@ struct ns_model {
     hipEvent_t graph_event = nullptr;
     bool shear_attr_set = false;     // hipFuncSetAttribute done for the Limber kernels
     std::bitset<192> fused_attr_set;  // ... and per instance of the one-kernel emulator
+    std::set<const void*> lds_attr_set;  // ... and of the digit-product kernels
     // BF16 tile / fused launch-shape choice per (kind, M, N, K, networks), measured at first use
     // or read from the on-disk cache (tune_path, entries of this GPU architecture only)
     std::map<std::tuple<int, int64_t, int, int, int>, int> tune;
@@ -346,6 +352,26 @@ __device__ __forceinline__ bool support_test(const SupportLoads& s, const double
     for (int j = 0; j < 8; ++j) ok = ok & !((s.k[j] == NS_PRIOR_UNIFORM) & ((s.t[j] < s.lo[j]) | (s.t[j] > s.hi[j])));
     return d > 8 ? ok & in_support(th + 8, d - 8, kind + 8, a + 8, b + 8) : ok;
 }
+
+// One-kernel FP64 forward and adjoint on int8 digits (mlp_i8.hip): false
+// without launching for other networks and for small batches.  tsave (may be
+// nullptr in the forward): pre-activations of hidden layer l + 1 of network g
+// at g net_stride + l slot_stride, [rows x 512].  The adjoint takes the output
+// deltas [rows x n_pad] of network g at g dstride to the first layer's [rows x 512].
+bool emulator_forward_digits(ns_model* m, const int* nets, int G, const double* theta, int64_t ld, int64_t B,
+                             void* const* outs, int64_t ldo, const int* is_log, double* tsave, size_t net_stride,
+                             size_t slot_stride, const int* count, hipStream_t s);
+bool emulator_backward_digits(ns_model* m, const int* nets, int G, int64_t B, const double* delta, double* delta1,
+                              size_t dstride, const double* tsave, size_t net_stride, size_t slot_stride,
+                              hipStream_t s);
+
+// Networks whose FP64 GEMM layers run as int8 digit products (gemm_i8.h):
+// every hidden width at least 256 (and even weights, see api.cpp).  Narrower layers stay on the FP64 MFMA: at
+// 128 inputs a tile's digit products take a quarter of the time, its 1024
+// conversions and activations the same.
+bool digit_shape(const std::vector<int>& dims);
+// Digit tiles and factors of the device matrix W64 [N x K] (K a multiple of 32).
+void digit_weights(const DevBuf& W64, int N, int K, DevBuf& tiles, DevBuf& back);
 
 // Networks the one-kernel FP64 forward supports: 3..8 layers, <= 16 inputs,
 // every hidden width 128, <= 256 outputs.
