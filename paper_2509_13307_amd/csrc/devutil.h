@@ -24,13 +24,68 @@ __device__ __forceinline__ uint16_t bf16_lo(float v, uint16_t hi) {
     return f2bf(v - bf2f(hi));
 }
 
-template <class T> __device__ __forceinline__ T sigmoid(T u) { return T(1) / (T(1) + exp(-u)); }
+// a b + c with the constant c taken from scalar registers: left to itself the
+// compiler copies each constant of a polynomial to vector registers first, two
+// moves per fused multiply-add
+__device__ __forceinline__ double fma_const(double a, double b, double c) {
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+    return d;
+}
+
+// 2^(x c), c = c_hi + c_lo, as 2^n p with p in [0.7, 1.42]: n = round(x c), the
+// rest f by two fused multiply-adds, 2^f = 1 + f q(f) with q of degree 10
+// interpolating (2^f - 1) / f at the Chebyshev nodes of [-1/2, 1/2] (error
+// 2e-17).  |x c| < 2^31.
+__device__ __forceinline__ double exp2_scaled(double x, double c_hi, double c_lo, int& n) {
+    const double t = fma(x, c_hi, 0x1.8p52);
+    const double m = t - 0x1.8p52;
+    const double f = fma(x, c_lo, fma(x, c_hi, -m));
+    n = __double2loint(t);
+    double q = fma_const(f, 0x1.e9d40bd1335b2p-32, 0x1.e6064f626db12p-28);
+    q = fma_const(q, f, 0x1.b524fadf5b6e0p-24);
+    q = fma_const(q, f, 0x1.62bfd46f7ae0cp-20);
+    q = fma_const(q, f, 0x1.ffcbfc6710084p-17);
+    q = fma_const(q, f, 0x1.4309130972778p-13);
+    q = fma_const(q, f, 0x1.5d87fe78a5272p-10);
+    q = fma_const(q, f, 0x1.3b2ab6fba1dd0p-7);
+    q = fma_const(q, f, 0x1.c6b08d704a0c2p-5);
+    q = fma_const(q, f, 0x1.ebfbdff82c598p-3);
+    q = fma_const(q, f, 0x1.62e42fefa39efp-1);
+    return fma(q, f, 1.0);
+}
+
+// 1 / (1 + exp(-u)).  FP64: half the instructions of the library's exp and
+// division (33 instead of 63 for the activation), which are what bounds the
+// layers' epilogues; u is held to [-700, 700] (outside, the sigmoid is 0 or 1
+// to 1e-304), a NaN stays one.
+template <class T> __device__ __forceinline__ T sigmoid(T u);
+template <> __device__ __forceinline__ double sigmoid<double>(double u) {
+    u = u > 700.0 ? 700.0 : u;
+    u = u < -700.0 ? -700.0 : u;
+    int n;
+    const double p = exp2_scaled(u, -0x1.71547652b82fep+0, -0x1.777d0ffda0d24p-56, n);
+    const double d = 1.0 + __hiloint2double(__double2hiint(p) + (n << 20), __double2loint(p));
+    // reciprocal: the hardware's estimate and two Newton steps
+    double y = __builtin_amdgcn_rcp(d);
+    y = fma(y, fma(-d, y, 1.0), y);
+    return fma(y, fma(-d, y, 1.0), y);
+}
 // FP32: hardware exp2 and reciprocal (about 1 ulp each)
 template <> __device__ __forceinline__ float sigmoid<float>(float u) {
     return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(u * -1.44269504088896341f));
 }
 // 10^y (output transform of log10-emulated spectra)
-template <class T> __device__ __forceinline__ T exp10_of(T y) { return exp(y * T(2.302585092994045684)); }
+template <class T> __device__ __forceinline__ T exp10_of(T y);
+// FP64: 2^(y log2 10), 23 instead of 57 instructions, and without the rounding
+// of y ln 10; beyond the range of a double it overflows and underflows alike
+template <> __device__ __forceinline__ double exp10_of<double>(double y) {
+    y = y > 400.0 ? 400.0 : y;
+    y = y < -400.0 ? -400.0 : y;
+    int n;
+    const double p = exp2_scaled(y, 0x1.a934f0979a371p+1, 0x1.7f2495fb7fa6dp-53, n);
+    return ldexp(p, n);
+}
 // FP32: 10^y = 2^(p_hi + p_lo) with p_hi = fl(y log2 10) and p_lo its rounding
 // residual (plus the residual of log2 10 itself), so that the argument
 // rounding (up to |y log2 10| 2^-24) does not reach the result; then
