@@ -719,7 +719,8 @@ static void launch_bf16_tuned(ns_model* m, int kind, const Group<Epi>& P, int64_
 }
 
 // kinds 2 .. 17: one-kernel forward, 2 + split + 2 wide + 4 chi^2 mode + 8
-// rounds of the sampler (rows a device count below the launch's maximum)
+// rounds of the sampler (rows a device count below the launch's maximum);
+// 18 .. 21: with the pre-activations kept for the adjoint
 int tune_ncfg(int kind) { return kind < 2 ? BF16_NCFG : fused_ncfg_of(((kind - 2) >> 1) & 1, (kind - 2) & 1); }
 const char* tune_cfg_name(int kind, int c) {
     return kind < 2 ? BF16_CFG_NAMES[c] : fused_cfg_name(((kind - 2) >> 1) & 1, (kind - 2) & 1, c);
@@ -731,11 +732,12 @@ std::string bf16_tuning_report(const ns_model* m) {
     for (const auto& kv : m->tune) {
         char tmp[256];
         const int kind = std::get<0>(kv.first);
-        static const char* kinds[18] = {
+        static const char* kinds[22] = {
             "bf16_hidden", "bf16_out", "fused_bf16", "fused_bf16x3", "fused_bf16", "fused_bf16x3",
             "fused_chi2_bf16", "fused_chi2_bf16x3", "fused_chi2_bf16", "fused_chi2_bf16x3",
             "fused_bf16 rounds", "fused_bf16x3 rounds", "fused_bf16 rounds", "fused_bf16x3 rounds",
-            "fused_chi2_bf16 rounds", "fused_chi2_bf16x3 rounds", "fused_chi2_bf16 rounds", "fused_chi2_bf16x3 rounds"};
+            "fused_chi2_bf16 rounds", "fused_chi2_bf16x3 rounds", "fused_chi2_bf16 rounds", "fused_chi2_bf16x3 rounds",
+            "fused_save_bf16", "fused_save_bf16x3", "fused_save_bf16", "fused_save_bf16x3"};
         const char* cfg = tune_cfg_name(kind, kv.second);
         snprintf(tmp, sizeof tmp, "%s\"%s M=%lld N=%d K=%d networks=%d\": \"%s\"", first ? "" : ", ", kinds[kind],
                  (long long)std::get<1>(kv.first), std::get<2>(kv.first), std::get<3>(kv.first),
@@ -844,6 +846,10 @@ void emulator_forward(ns_model* m, const int* nets, int G, const double* theta, 
     auto tslot = [&](int g, int slot) -> void* {
         return tbase ? (void*)(tbase + ((size_t)g * save_stride + (size_t)slot * act_stride) * tsz) : nullptr;
     };
+    if (save_t && getenv("NSMI_NO_FUSED_MLP") == nullptr &&
+        emulator_forward_fused(m, nets, G, theta, ld, B, outs, ldo, is_log, prec, count, s, (float*)tbase, save_stride,
+                               act_stride))
+        return;
     if (prec == NS_FP64 && emulator_forward_digits(m, nets, G, theta, ld, B, outs, ldo, is_log, (double*)tbase,
                                                    save_stride, act_stride, count, s))
         return;

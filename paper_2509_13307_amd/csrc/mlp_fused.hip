@@ -38,9 +38,11 @@ struct FusedNet {
     const float* vec;      // hidden layer l: b, beta, gamma at l 3H + {0, H, 2H}; output bias after them
     const float* mu; const float* sigma;
     float* out; int is_log;
+    float* t;              // pre-activations of hidden layer l + 1 at l tslot, [rows x H] (SAVE)
 };
 
 struct FusedArgs {
+    int64_t tslot;
     FusedNet net[4];
     int n_hidden;        // hidden GEMM layers (network layers - 2)
     int n_in, N_out, mu_rows;
@@ -111,7 +113,8 @@ bool fused_shape(const std::vector<int>& dims) {
     return true;
 }
 
-template <int H, int RT, bool X3, int P, int CT, bool CHI>
+// CHI: the chi^2 epilogue; SAVE: the pre-activations are stored for the adjoint.
+template <int H, int RT, bool X3, int P, int CT, bool CHI, bool SAVE>
 __global__ __launch_bounds__(2 * H / CT) void mlp_fused_kernel(
     const double* __restrict__ theta, int64_t ld, int64_t rows, int rows_per_walker, const int* __restrict__ src,
     const double* __restrict__ fix, const double* __restrict__ znodes, FusedArgs A, const int* __restrict__ count) {
@@ -218,6 +221,7 @@ __global__ __launch_bounds__(2 * H / CT) void mlp_fused_kernel(
 #pragma unroll
             for (int j = 0; j < FU; ++j) {
                 const int rr = rr0 + (j0 + j) * RS;
+                if (SAVE && rr < nvalid) N.t[(r0 + rr) * H + c] = acc[j];
                 const float v = gated<float>(acc[j], be1, ga1);
                 const uint16_t hi = f2bf(v);
                 hs[rr * HS + c] = hi;
@@ -380,6 +384,20 @@ __global__ __launch_bounds__(2 * H / CT) void mlp_fused_kernel(
     // epilogue of hidden segment v: gated activation of this wave's units, the
     // BF16 (hi, lo) split into LDS
     auto hidden_epi = [&]() {
+        if (SAVE) {
+            float* tb = N.t + (v + 1) * A.tslot + r0 * H;
+#pragma unroll
+            for (int j = 0; j < CT; ++j) {
+                const unsigned lofs = (unsigned)((lane >> 5) * 4 * H + wave * WC + j * 32 + (lane & 31));
+#pragma unroll
+                for (int i = 0; i < RT; ++i)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int lr = i * 32 + (r >> 2) * 8 + (r & 3);
+                        if (nvalid == R || lr + (lane >> 5) * 4 < nvalid) (tb + lr * H)[lofs] = acc[i][j][r] + e0[j];
+                    }
+            }
+        }
 #pragma unroll
         for (int j = 0; j < CT; ++j) {
             const int c = wave * WC + j * 32 + (lane & 31);
@@ -555,7 +573,7 @@ __global__ __launch_bounds__(256) void chi2_fused_finish_kernel(const double* __
     A.logl[r] = !ok ? -INFINITY : (A.chi == 1 ? -0.5 * sum + A.cst : A.cst - sum);
 }
 
-template <int H, int RT, bool X3, int P, int CT, bool CHI>
+template <int H, int RT, bool X3, int P, int CT, bool CHI, bool SAVE = false>
 static void launch_fused(ns_model* m, const FusedArgs& A, const double* theta, int64_t ld, int64_t rows, int rpw,
                          int G, const int* count, hipStream_t s) {
     constexpr int R = 32 * RT;
@@ -563,14 +581,9 @@ static void launch_fused(ns_model* m, const FusedArgs& A, const double* theta, i
     const size_t base = (size_t)(X3 ? 2 : 1) * R * (H + 8) * sizeof(uint16_t) + FM_SLACK;
     const size_t slots = (size_t)R * (H / 32) * sizeof(double);     // chi^2 mode's row sums
     const size_t smem = base + (CHI ? slots : 0);
-    const auto kern = mlp_fused_kernel<H, RT, X3, P, CT, CHI>;
-    const int rtc = RT == 2 ? 0 : (RT == 1 ? 1 : 2);
-    const int bit = ((((int)CHI * 3 + rtc) * 2 + (H == 512)) * 2 + X3) * 8 + (CT == 1) * 4 +
-                    (P == 2 ? 0 : (P == 4 ? 1 : 2));
-    if (smem > 64 * 1024 && !m->fused_attr_set[bit]) {
+    const auto kern = mlp_fused_kernel<H, RT, X3, P, CT, CHI, SAVE>;
+    if (smem > 64 * 1024 && m->lds_attr_set.insert((const void*)kern).second)
         NS_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-        m->fused_attr_set[bit] = true;
-    }
     const dim3 grid((unsigned)((rows + R - 1) / R), (unsigned)G, (unsigned)A.qg);
     hipLaunchKernelGGL(kern, grid, dim3(NT), smem, s, theta, ld, rows, rpw, m->emu_src_d.as<int>(),
                        m->emu_fix_d.as<double>(), m->znodes_d.as<double>(), A, count);
@@ -587,10 +600,21 @@ static void launch_fused(ns_model* m, const FusedArgs& A, const double* theta, i
 // identical results.
 using FusedLaunch = void (*)(ns_model*, const FusedArgs&, const double*, int64_t, int64_t, int, int, const int*,
                              hipStream_t);
-struct FusedCfg { FusedLaunch fn, fn_chi; const char* name; bool split_out; };
+// fn_save (nullptr where the hidden layers run once per output block, which
+// would store the pre-activations as often): the launch for a gradient, which
+// also stores every hidden pre-activation.  Four 6-512^4-2500 networks, split
+// form, 4 096 rows: 280 us, 134 MB of stores included, against 492 us for the
+// layer-by-layer launches it replaced (their FP32 activations pass through
+// memory between layers and are split again by every tile that reads them).
+struct FusedCfg { FusedLaunch fn, fn_chi, fn_save; const char* name; bool split_out; };
 template <int H, int RT, bool X3, int P, int CT>
-constexpr FusedCfg fcfg(const char* name, bool split_out = false) {
-    return {launch_fused<H, RT, X3, P, CT, false>, launch_fused<H, RT, X3, P, CT, true>, name, split_out};
+constexpr FusedCfg fcfg(const char* name) {
+    return {launch_fused<H, RT, X3, P, CT, false>, launch_fused<H, RT, X3, P, CT, true>,
+            launch_fused<H, RT, X3, P, CT, false, true>, name, false};
+}
+template <int H, int RT, bool X3, int P, int CT>
+constexpr FusedCfg fcfg_split(const char* name) {
+    return {launch_fused<H, RT, X3, P, CT, false>, launch_fused<H, RT, X3, P, CT, true>, nullptr, name, true};
 }
 constexpr int FUSED_NCFG = 10;                    // table width; the split form at width 512 has 8 candidates
 static int fused_ncfg(int h512, int x3) { return x3 && h512 ? 8 : 10; }
@@ -604,8 +628,8 @@ static const FusedCfg FUSED_CFGS[2][2][FUSED_NCFG] = {
          fcfg<128, 1, false, 8, 1>("fused 4 waves x 32 units, 32 rows, prefetch 8"),
          fcfg<128, 4, false, 4, 1>("fused 4 waves x 32 units, 128 rows, prefetch 4"),
          fcfg<128, 4, false, 4, 2>("fused 2 waves x 64 units, 128 rows, prefetch 4"),
-         fcfg<128, 1, false, 4, 1>("fused 4 waves x 32 units, 32 rows, prefetch 4, output blocks split", true),
-         fcfg<128, 1, false, 8, 1>("fused 4 waves x 32 units, 32 rows, prefetch 8, output blocks split", true)},
+         fcfg_split<128, 1, false, 4, 1>("fused 4 waves x 32 units, 32 rows, prefetch 4, output blocks split"),
+         fcfg_split<128, 1, false, 8, 1>("fused 4 waves x 32 units, 32 rows, prefetch 8, output blocks split")},
         {fcfg<128, 2, true, 2, 2>("fused split 2 waves x 64 units, prefetch 2"),
          fcfg<128, 2, true, 4, 2>("fused split 2 waves x 64 units, prefetch 4"),
          fcfg<128, 2, true, 2, 1>("fused split 4 waves x 32 units, prefetch 2"),
@@ -614,8 +638,8 @@ static const FusedCfg FUSED_CFGS[2][2][FUSED_NCFG] = {
          fcfg<128, 1, true, 4, 1>("fused split 4 waves x 32 units, 32 rows, prefetch 4"),
          fcfg<128, 1, true, 8, 1>("fused split 4 waves x 32 units, 32 rows, prefetch 8"),
          fcfg<128, 2, true, 8, 1>("fused split 4 waves x 32 units, prefetch 8"),
-         fcfg<128, 1, true, 2, 1>("fused split 4 waves x 32 units, 32 rows, prefetch 2, output blocks split", true),
-         fcfg<128, 1, true, 8, 1>("fused split 4 waves x 32 units, 32 rows, prefetch 8, output blocks split", true)},
+         fcfg_split<128, 1, true, 2, 1>("fused split 4 waves x 32 units, 32 rows, prefetch 2, output blocks split"),
+         fcfg_split<128, 1, true, 8, 1>("fused split 4 waves x 32 units, 32 rows, prefetch 8, output blocks split")},
     },
     {   // H = 512
         {fcfg<512, 2, false, 4, 2>("fused 8 waves x 64 units, prefetch 4"),
@@ -626,16 +650,16 @@ static const FusedCfg FUSED_CFGS[2][2][FUSED_NCFG] = {
          fcfg<512, 1, false, 8, 1>("fused 16 waves x 32 units, 32 rows, prefetch 8"),
          fcfg<512, 4, false, 4, 1>("fused 16 waves x 32 units, 128 rows, prefetch 4"),
          fcfg<512, 4, false, 4, 2>("fused 8 waves x 64 units, 128 rows, prefetch 4"),
-         fcfg<512, 1, false, 4, 1>("fused 16 waves x 32 units, 32 rows, prefetch 4, output blocks split", true),
-         fcfg<512, 1, false, 8, 1>("fused 16 waves x 32 units, 32 rows, prefetch 8, output blocks split", true)},
+         fcfg_split<512, 1, false, 4, 1>("fused 16 waves x 32 units, 32 rows, prefetch 4, output blocks split"),
+         fcfg_split<512, 1, false, 8, 1>("fused 16 waves x 32 units, 32 rows, prefetch 8, output blocks split")},
         {fcfg<512, 2, true, 2, 2>("fused split 8 waves x 64 units, prefetch 2"),
          fcfg<512, 2, true, 4, 2>("fused split 8 waves x 64 units, prefetch 4"),
          fcfg<512, 2, true, 2, 1>("fused split 16 waves x 32 units, prefetch 2"),
          fcfg<512, 2, true, 4, 1>("fused split 16 waves x 32 units, prefetch 4"),
          fcfg<512, 1, true, 2, 1>("fused split 16 waves x 32 units, 32 rows, prefetch 2"),
          fcfg<512, 1, true, 4, 1>("fused split 16 waves x 32 units, 32 rows, prefetch 4"),
-         fcfg<512, 1, true, 2, 1>("fused split 16 waves x 32 units, 32 rows, prefetch 2, output blocks split", true),
-         fcfg<512, 1, true, 4, 1>("fused split 16 waves x 32 units, 32 rows, prefetch 4, output blocks split", true)},
+         fcfg_split<512, 1, true, 2, 1>("fused split 16 waves x 32 units, 32 rows, prefetch 2, output blocks split"),
+         fcfg_split<512, 1, true, 4, 1>("fused split 16 waves x 32 units, 32 rows, prefetch 4, output blocks split")},
     },
 };
 
@@ -687,7 +711,7 @@ static void fused_run(ns_model* m, const FusedArgs& A, int H, bool x3, int G, co
     auto run_rows = [&](int c, int64_t nr, const int* cnt) {
         FusedArgs Ac = A;
         Ac.qg = cfgs[c].split_out ? ncb : 1;
-        (Ac.chi ? cfgs[c].fn_chi : cfgs[c].fn)(m, Ac, theta, ld, nr, rpw, G, cnt, s);
+        (Ac.chi ? cfgs[c].fn_chi : Ac.tslot ? cfgs[c].fn_save : cfgs[c].fn)(m, Ac, theta, ld, nr, rpw, G, cnt, s);
         if (Ac.chi && Ac.qg > 1)
             hipLaunchKernelGGL(chi2_fused_finish_kernel, dim3((unsigned)((nr + 255) / 256)), dim3(256), 0, s,
                                (const double*)Ac.part, ncb, H / 32, nr, Ac, cnt);
@@ -696,13 +720,16 @@ static void fused_run(ns_model* m, const FusedArgs& A, int H, bool x3, int G, co
     // a sampler round's launch (rows a device count) is tuned apart from an
     // exact batch of the same maximum: the initial live points and the rounds
     // of 2 x speculation x k walkers can share one row count
-    const auto key = std::make_tuple(2 + (int)x3 + 2 * h512 + (A.chi ? 4 : 0) + (count ? 8 : 0), rows, A.N_out, H, G);
+    const auto key = std::make_tuple(2 + (int)x3 + 2 * h512 + (A.tslot ? 16 : (A.chi ? 4 : 0) + (count ? 8 : 0)), rows,
+                                     A.N_out, H, G);
+    auto has = [&](int c) { return !A.tslot || cfgs[c].fn_save; };
     int best = 0;
     auto it = m->tune.find(key);
     const char* forced = getenv("NSMI_FUSED_CFG");      // pin one candidate (tests of every shape)
     if (forced != nullptr) {
         best = std::min(std::max(atoi(forced), 0), fused_ncfg(h512, x3) - 1);
-    } else if (it != m->tune.end()) {
+        if (!has(best)) best = 0;
+    } else if (it != m->tune.end() && has(it->second)) {
         best = it->second;
     } else {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -734,6 +761,7 @@ static void fused_run(ns_model* m, const FusedArgs& A, int H, bool x3, int G, co
                 for (int c = 0; c < ncfg; ++c) best_ms[c] = 1e30f;
                 for (int pass = 0; pass < 2; ++pass)
                     for (int c = 0; c < ncfg; ++c) {
+                        if (!has(c)) continue;
                         run_rows(c, nr, nullptr);
                         NS_HIP(hipEventRecord(e0, s));
                         for (int r = 0; r < 4; ++r) run_rows(c, nr, nullptr);
@@ -746,13 +774,13 @@ static void fused_run(ns_model* m, const FusedArgs& A, int H, bool x3, int G, co
                 for (int c = 0; c < ncfg; ++c) tot_ms[c] += best_ms[c];
             }
             for (int c = 1; c < ncfg; ++c)
-                if (tot_ms[c] < tot_ms[best]) best = c;
+                if (tot_ms[c] < tot_ms[best]) best = c;    // (a candidate that was not run has 1e30)
             (void)hipEventDestroy(e0);
             (void)hipEventDestroy(e1);
             tune_cache_store(m, key, best);
         }
     }
-    TraceScope ts(m, s, A.chi ? (x3 ? "mlp_fused_chi2_bf16x3" : "mlp_fused_chi2_bf16")
+    TraceScope ts(m, s, A.tslot ? (x3 ? "mlp_fused_save_bf16x3" : "mlp_fused_save_bf16") : A.chi ? (x3 ? "mlp_fused_chi2_bf16x3" : "mlp_fused_chi2_bf16")
                               : (x3 ? "mlp_fused_bf16x3" : "mlp_fused_bf16"));
     run(best);
     NS_HIP(hipGetLastError());
@@ -762,13 +790,15 @@ static void fused_run(ns_model* m, const FusedArgs& A, int H, bool x3, int G, co
 // ordered weights (shape outside fused_shape) or the form is not BF16-operand.
 bool emulator_forward_fused(ns_model* m, const int* nets, int G, const double* theta, int64_t ld, int64_t B,
                             void* const* outs, int64_t ldo, const int* is_log, int prec, const int* count,
-                            hipStream_t s) {
+                            hipStream_t s, float* tsave, size_t net_stride, size_t slot_stride) {
     if (prec != NS_BF16 && prec != NS_BF16X3) return false;
     const Net& n0 = *m->nets[nets[0]];
     if (!n0.fused) return false;
     FusedArgs A = fused_args(m, nets, G);
     A.ldo = ldo;
+    A.tslot = tsave ? (int64_t)slot_stride : 0;
     for (int g = 0; g < G; ++g) {
+        A.net[g].t = tsave ? tsave + g * net_stride : nullptr;
         A.net[g].out = static_cast<float*>(outs[g]);
         A.net[g].is_log = is_log[g];
     }

@@ -6,7 +6,6 @@
 #include <stdint.h>
 
 #include <algorithm>
-#include <bitset>
 #include <cmath>
 #include <cstddef>
 #include <cstring>
@@ -189,8 +188,7 @@ struct ns_model {
     hipStream_t graph_stream = nullptr;  // stream the captured sampler graphs replay on
     hipEvent_t graph_event = nullptr;
     bool shear_attr_set = false;     // hipFuncSetAttribute done for the Limber kernels
-    std::bitset<192> fused_attr_set;  // ... and per instance of the one-kernel emulator
-    std::set<const void*> lds_attr_set;  // ... and of the digit-product kernels
+    std::set<const void*> lds_attr_set;  // ... and per instance of the emulator kernels
     // BF16 tile / fused launch-shape choice per (kind, M, N, K, networks), measured at first use
     // or read from the on-disk cache (tune_path, entries of this GPU architecture only)
     std::map<std::tuple<int, int64_t, int, int, int>, int> tune;
@@ -236,10 +234,10 @@ void emulator_forward(ns_model* m, const int* nets, int G, const double* theta, 
 bool fused_shape(const std::vector<int>& dims);
 // Whole-network forward in one kernel for NS_BF16 / NS_BF16X3 (activations
 // resident in LDS); returns false without launching when the form or the
-// network shape does not fit it.
+// network shape does not fit it.  tsave: as for emulator_forward_digits, FP32.
 bool emulator_forward_fused(ns_model* m, const int* nets, int G, const double* theta, int64_t ld, int64_t B,
                             void* const* outs, int64_t ldo, const int* is_log, int prec, const int* count,
-                            hipStream_t s);
+                            hipStream_t s, float* tsave = nullptr, size_t net_stride = 0, size_t slot_stride = 0);
 // Emulator and chi^2 in one launch for the one-network CMB kinds (diagonal
 // Gaussian, cosmic-variance TT) in the BF16-operand forms: logL [B] written;
 // false (nothing launched) for other models or forms, or with
@@ -394,7 +392,7 @@ int fused_ncfg_of(int h512, int x3);
 std::string bf16_tuning_report(const ns_model* m);
 
 // Autotuner tables: candidates of tuning kind `kind` (0 BF16 hidden GEMM,
-// 1 BF16 output GEMM, 2 + split + 2 wide + 4 chi^2 mode + 8 sampler rounds:
+// 1 BF16 output GEMM, 2 + split + 2 wide + 4 chi^2 mode + 8 sampler rounds, 18 + split + 2 wide gradients:
 // one-kernel emulator) and their names.
 int tune_ncfg(int kind);
 const char* tune_cfg_name(int kind, int c);
