@@ -474,16 +474,19 @@ __global__ __launch_bounds__(512) void mlp_i8_back_kernel(int64_t rows, int n_pa
 }
 
 // Networks the one-kernel forms take: every hidden width 512, at most six
-// hidden GEMM layers; batches whose row blocks fill 9/16 of the CUs (a network
-// takes one workgroup 330 us whatever the batch, and the layer-by-layer
-// launches, which split each layer over all CUs, grow with it: 2 500 outputs,
-// 4 096 rows, 128 blocks: 309 against 348 us; 6 144 rows, 192 blocks: 620
-// against 385 us).
-static bool digit_one_kernel(const ns_model* m, const Net& n0, int G, int64_t rows) {
+// hidden GEMM layers; batches whose row blocks fill 13/32 of the CUs (the
+// adjoint: 5/16).  A network takes one workgroup the same time whatever the
+// batch, and the layer-by-layer launches, which split each layer over all CUs,
+// grow with it.  One network, layered against one kernel, us: 2 500 outputs
+// forward 301 / 318 at 2 880 rows, 313 / 319 at 3 520, 509 / 333 at 4 160, and
+// adjoint 307 / 340 at 2 240, 345 / 342 at 2 880, 390 / 345 at 3 520; 200
+// outputs forward 188 / 186 at 2 880, 208 / 187 at 3 520, and adjoint
+// 116 / 176 at 1 600, 197 / 176 at 2 240, 213 / 176 at 2 880.
+static bool digit_one_kernel(const ns_model* m, const Net& n0, int G, int64_t rows, bool back) {
     if (!n0.digits || n0.n_layers < 3 || n0.n_layers - 2 > DM_MAXHID) return false;
     for (int l = 1; l < n0.n_layers; ++l)
         if (n0.dims[l] != DM_H) return false;
-    return (rows + DG_ROWS - 1) / DG_ROWS * G * 16 >= 9 * (int64_t)device_cus(m->device);
+    return (rows + DG_ROWS - 1) / DG_ROWS * G * 32 >= (back ? 10 : 13) * (int64_t)device_cus(m->device);
 }
 
 bool emulator_forward_digits(ns_model* m, const int* nets, int G, const double* theta, int64_t ld, int64_t B,
@@ -492,7 +495,7 @@ bool emulator_forward_digits(ns_model* m, const int* nets, int G, const double* 
     const Net& n0 = *m->nets[nets[0]];
     const int L = n0.n_layers, rpw = n0.out_mu_rows;
     const int64_t rows = B * rpw;
-    if (!digit_one_kernel(m, n0, G, rows)) return false;
+    if (!digit_one_kernel(m, n0, G, rows, false)) return false;
     DigitArgs A{};
     A.n_hidden = L - 2;
     A.n_in = n0.dims[0];
@@ -544,7 +547,7 @@ bool emulator_backward_digits(ns_model* m, const int* nets, int G, int64_t B, co
     const Net& n0 = *m->nets[nets[0]];
     const int L = n0.n_layers, rpw = n0.out_mu_rows;
     const int64_t rows = B * rpw;
-    if (!digit_one_kernel(m, n0, G, rows)) return false;
+    if (!digit_one_kernel(m, n0, G, rows, true)) return false;
     DigitArgs A{};
     A.n_hidden = L - 2;
     A.nrb = (int)((rows + DG_ROWS - 1) / DG_ROWS);
