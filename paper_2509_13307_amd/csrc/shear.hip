@@ -190,8 +190,8 @@ __global__ __launch_bounds__(256) void zspline_reg_kernel(const T* __restrict__ 
 //     is summed on the way.
 // The windows are linear in n_i, so the normalisations are applied to the
 // spectra.  Output per walker: the scaled windows [nb][n_a] (the Limber
-// integrand is the product of two of them and P), log10 chi_j [n_a] and the
-// normalisations [nb].
+// integrand is the product of two of them and P), log10 chi_j [n_a], the
+// normalisations [nb] and 1 + m_i [nb].
 template <class T, int KMAX>
 __global__ __launch_bounds__(256, 2) void shear_windows_kernel(
     const double* __restrict__ theta, int64_t ld, int64_t B, ShearGeom G,
@@ -221,10 +221,10 @@ __global__ __launch_bounds__(256, 2) void shear_windows_kernel(
     // E, f and the growth integrand at scale factor a (ln a given)
     auto bg = [&](double a, double la, double& E, double& f, double& g) {
         const double ia = 1.0 / a, ia2 = ia * ia, ia3 = ia2 * ia;
-        const double E2 = Om * ia3 + (1.0 - Om) * exp(pde * la - 3.0 * wa * (1.0 - a));
+        const double E2 = Om * ia3 + (1.0 - Om) * exp_of(pde * la - 3.0 * wa * (1.0 - a));
         E = sqrt(E2);
         f = cH0 * ia2 / E;
-        g = exp(GROWTH_INDEX * log(Om * ia3 / E2)) * ia;
+        g = exp_of(GROWTH_INDEX * log(Om * ia3 / E2)) * ia;
     };
 
     // (1) S0 E_j, S1 f_j, S2 growth integrand; S3, S4 the Simpson increments
@@ -271,12 +271,7 @@ __global__ __launch_bounds__(256, 2) void shear_windows_kernel(
                 X[r * 64 + lane] = run;
                 run += x;
             }
-        double inc = run;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const double y = __shfl_up(inc, off, 64);
-            if (lane >= off) inc += y;
-        }
+        const double inc = wave_scan(run);
         const double up = __shfl_up(inc, 1, 64), ex = lane > 0 ? up : 0.0;
         for (int r = 0; r < k; ++r)
             if (lane * k + r < na) X[r * 64 + lane] += ex;
@@ -290,7 +285,7 @@ __global__ __launch_bounds__(256, 2) void shear_windows_kernel(
         const int p = t + 256 * u;
         const int j = (p & 63) * k + (p >> 6);
         if (p >= L || j >= na) continue;
-        const double a = agrid[j], E = S0[p], f = S1[p], chi = S3[p], D = exp(-S4[p]);
+        const double a = agrid[j], E = S0[p], f = S1[p], chi = S3[p], iD = exp_of(S4[p]);
         const double ia = 1.0 / a, ia2 = ia * ia;
         const double q = (j == 0 || j == na - 1) ? 0.5 * G.da : G.da;
         const bool in = j > 0;
@@ -301,7 +296,7 @@ __global__ __launch_bounds__(256, 2) void shear_windows_kernel(
         S2[p] = in ? ia2 / chi : 0.0;
         S3[p] = sw * pref;
         S4[p] = sw * pref * chi;
-        S5[p] = -sw * C1_RHOCR * Om * H0c * E / D;
+        S5[p] = -sw * C1_RHOCR * Om * H0c * E * iD;
         lchi_out[w * na + j] = in ? log10(chi) : 0.0;
     }
     __syncthreads();
@@ -310,7 +305,7 @@ __global__ __launch_bounds__(256, 2) void shear_windows_kernel(
     const double is2 = 1.0 / (2.0 * G.nz_sigma * G.nz_sigma), hda = 0.5 * G.da;
     const int j0 = lane * k;
     for (int i = wid; i < nb; i += NW) {
-        const double mu = nz_mean[i] + phys(9 + nb + i), AIA = phys(9 + i);
+        const double mu = nz_mean[i] + phys(9 + nb + i), AIA = phys(9 + i), mi = phys(9 + 2 * nb + i);
         double nrv[KMAX];
 #pragma unroll
         for (int r = 0; r < KMAX; ++r) {      // unnormalised n_i(z_j), 0 at z = 0
@@ -318,7 +313,7 @@ __global__ __launch_bounds__(256, 2) void shear_windows_kernel(
             double v = 0.0;
             if (r < k && j > 0 && j < na) {
                 const double dz = S0[r * 64 + lane] - mu;
-                v = exp(-dz * dz * is2);
+                v = exp_of(-dz * dz * is2);
             }
             nrv[r] = v;
         }
@@ -374,7 +369,10 @@ __global__ __launch_bounds__(256, 2) void shear_windows_kernel(
             x1 = g1;
         }
         const double v = wave_sum(nsum);
-        if (lane == 0) norm_out[w * nb + i] = v;
+        if (lane == 0) {
+            norm_out[w * 2 * nb + i] = v;
+            norm_out[w * 2 * nb + nb + i] = 1.0 + mi;
+        }
     }
 }
 
@@ -382,13 +380,13 @@ __global__ __launch_bounds__(256, 2) void shear_windows_kernel(
 // nodes).  (c) thread = node: log10 P carried to z_j (cubic spline or linear
 // in z), Catmull-Rom in log10 k at k = (l + 1/2)/chi_j, P = 10^(.), zero
 // outside [k_min, k_max]; [256][LB] in LDS with the chunk's scaled windows.
-// (d) thread = (pair, node segment): all LB multipoles of one pair in
-// registers, C_ij(l) += W~_i W~_j P(l); the segments are added in a fixed
+// (d) thread = (two pairs, FP64 one, node segment): all LB multipoles of each
+// in registers (bound by reading P from LDS, which two pairs share; segments
+// four elements apart in their bank), C_ij(l) += W~_i W~_j P(l); the segments are added in a fixed
 // order, times (1 + m_i)(1 + m_j) / (N_i N_j) with the n(z) normalisations N.
 template <class T, bool LINZ, int LB>
 __global__ __launch_bounds__(256) void limber_sum_kernel(
-    const double* __restrict__ theta, int64_t ld, int64_t B, ShearGeom G,
-    const int* __restrict__ pidx, const double* __restrict__ pfix, const int* __restrict__ zidx,
+    int64_t B, ShearGeom G, const int* __restrict__ zidx,
     const double* __restrict__ zcoef, const double* __restrict__ lell, const T* __restrict__ Ytab,
     const T* __restrict__ Mtab, const T* __restrict__ Win, const double* __restrict__ lchi_in,
     const double* __restrict__ norm_in, double* __restrict__ Cout, double* __restrict__ part,
@@ -401,9 +399,9 @@ __global__ __launch_bounds__(256) void limber_sum_kernel(
     const int na = G.n_a, nb = G.n_bins, npr = G.n_pairs, nl = G.n_ell;
     const int nch = (na + 255) / 256, c = blockIdx.y;    // this workgroup's chunk of nodes
     constexpr int WS = 257;                                           // padded row of the window table
-    T* Ws = reinterpret_cast<T*>(smem);                               // [nb][WS]
-    T* Pl = Ws + nb * WS;                                             // [256][LB]
-    auto phys = [&](int slot) { const int ix = pidx[slot]; return ix >= 0 ? theta[w * ld + ix] : pfix[slot]; };
+    auto scale = reinterpret_cast<double2*>(smem);                    // (1 + m_i)(1 + m_j), N_i N_j of each pair
+    T* Ws = reinterpret_cast<T*>(smem + npr * sizeof(double2));       // [nb][WS]
+    T* Pl = Ws + (nb * WS + 3) / 4 * 4;                               // [256][LB], 4 elements more after each segment
     auto pair_of = [&](int p, int& bi, int& bj) {
         int rem = p;
         bi = 0;
@@ -412,13 +410,27 @@ __global__ __launch_bounds__(256) void limber_sum_kernel(
     };
     const int nseg = max(1, 256 / npr);
     const int len = (256 + nseg - 1) / nseg;
-    const bool worker = t < npr * nseg;
-    const int pw = t % npr, sg = t / npr;
-    int bi = 0, bj = 0;
-    if (worker) pair_of(pw, bi, bj);
-    T acc[LB];
+    constexpr int PG = sizeof(T) == 4 ? 2 : 1;           // pairs per thread
+    const int npg = (npr + PG - 1) / PG;
+    const bool worker = t < npg * nseg;
+    const int pw = PG * (t % npg), sg = t / npg;
+    int bi[PG] = {}, bj[PG] = {};
+    if (worker)
 #pragma unroll
-    for (int e = 0; e < LB; ++e) acc[e] = T(0);
+        for (int q = 0; q < PG; ++q) pair_of(min(pw + q, npr - 1), bi[q], bj[q]);
+    // factors of pair t, in flight during the lookups
+    double si = 0.0, sj = 0.0, ni = 1.0, nj = 1.0;
+    if (t < npr && nch == 1) {
+        int ci, cj;
+        pair_of(t, ci, cj);
+        const double* nm = norm_in + w * 2 * nb;
+        ni = nm[ci]; nj = nm[cj]; si = nm[nb + ci]; sj = nm[nb + cj];
+    }
+    T acc[PG][LB];
+#pragma unroll
+    for (int q = 0; q < PG; ++q)
+#pragma unroll
+        for (int e = 0; e < LB; ++e) acc[q][e] = T(0);
     const int64_t tab = w * (int64_t)G.n_z * G.n_k;
     {
         const int j = c * 256 + t;
@@ -430,96 +442,114 @@ __global__ __launch_bounds__(256) void limber_sum_kernel(
         const int zc = live ? 4 * j : 0;
         const T c0 = (T)zcoef[zc], c1 = (T)zcoef[zc + 1];
         const T c2 = LINZ ? T(0) : (T)zcoef[zc + 2], c3 = LINZ ? T(0) : (T)zcoef[zc + 3];
-        const T* y0 = Ytab + tab + (int64_t)n * G.n_k;
-        const T* m0p = LINZ ? y0 : Mtab + tab + (int64_t)n * G.n_k;
-        // log10 P at z_j from rows n, n + 1 of Y (and of M for cubic z)
-        auto zmix = [&](T ya, T yb, T ma, T mb) {
-            if (LINZ) return c0 * ya + c1 * yb;
-            return c0 * ya + c1 * yb + c2 * ma + c3 * mb;
-        };
-        auto Yz = [&](int col) {
-            return zmix(y0[col], y0[col + G.n_k], LINZ ? T(0) : m0p[col], LINZ ? T(0) : m0p[col + G.n_k]);
-        };
-        // the four columns i0 - 1 .. i0 + 2 of one row in one load each (the
-        // rows are only element-aligned; the target allows such vector loads)
+        // rows n, n + 1 of Y (and of M for cubic z): uniform bases, one 32-bit lane offset
+        const char* Y0 = reinterpret_cast<const char*>(Ytab + tab);
+        const char* Y1 = Y0 + G.n_k * sizeof(T);
+        const char* M0 = LINZ ? Y0 : reinterpret_cast<const char*>(Mtab + tab);
+        const char* M1 = M0 + G.n_k * sizeof(T);
+        const unsigned row = (unsigned)(n * G.n_k) * (unsigned)sizeof(T);
+        const double rdu = 1.0 / G.du;
         struct Q4 { T v[4]; };
-        auto row4 = [&](const T* p) { Q4 q; __builtin_memcpy(&q, p, sizeof(q)); return q; };
-#pragma unroll 4
-        for (int b = 0; b < LB; ++b) {
-            T P = T(0);
-            const double lk = b < nl ? lell[b] - lchi : 0.0;
-            if (live && b < nl && lk >= G.u0 && lk <= G.u1) {
-                const double sv = (lk - G.u0) / G.du;
+        T* Pt = Pl + t * LB + t / len * 4;
+        // Without branches, so that the gathers of UL lookups are in flight
+        // together: four columns c .. c + 3 around the interval [i0, i0 + 1],
+        // moved inside the grid at its ends (n_k >= 4), where the neighbour
+        // beyond is the linear continuation; a lookup outside [k_min, k_max]
+        // reads the nearest columns and counts 0.  16384 walkers of 256 nodes,
+        // FP32, cubic: 265 us with two in flight, 291 with one, 296 with four
+        // (fewer waves fit), 355 with the branches (a wait per lookup); 500
+        // walkers of 1025 nodes, FP64, linear: 132, 146, 122, 189.
+        constexpr int UL = LINZ ? 4 : 2;
+        static_assert(LB % UL == 0, "whole groups of lookups");
+#pragma unroll 1
+        for (int b0 = 0; b0 < LB; b0 += UL) {
+            Q4 ya[UL], yb[UL], ma[UL], mb[UL];
+            T tt[UL];
+            bool in[UL], lo[UL], hi[UL];
+#pragma unroll
+            for (int u = 0; u < UL; ++u) {
+                const double lk = lell[min(b0 + u, nl - 1)] - lchi;
+                in[u] = live && b0 + u < nl && lk >= G.u0 && lk <= G.u1;
+                // (lk - u0) / du: one correction of the reciprocal's product rounds as the division does
+                const double x = lk - G.u0, q0 = x * rdu, sv = fma(fma(-q0, G.du, x), rdu, q0);
                 int i0 = (int)floor(sv);
-                i0 = i0 < 0 ? 0 : (i0 > G.n_k - 2 ? G.n_k - 2 : i0);
-                const T tt = (T)(sv - i0);
-                T pm, p0, p1, p2;
-                if (i0 > 0 && i0 + 2 < G.n_k) {
-                    const Q4 ya = row4(y0 + i0 - 1), yb = row4(y0 + G.n_k + i0 - 1);
-                    Q4 ma = {}, mb = {};
-                    if (!LINZ) {
-                        ma = row4(m0p + i0 - 1);
-                        mb = row4(m0p + G.n_k + i0 - 1);
-                    }
-                    pm = zmix(ya.v[0], yb.v[0], ma.v[0], mb.v[0]);
-                    p0 = zmix(ya.v[1], yb.v[1], ma.v[1], mb.v[1]);
-                    p1 = zmix(ya.v[2], yb.v[2], ma.v[2], mb.v[2]);
-                    p2 = zmix(ya.v[3], yb.v[3], ma.v[3], mb.v[3]);
-                } else {
-                    p0 = Yz(i0);
-                    p1 = Yz(i0 + 1);
-                    pm = i0 > 0 ? Yz(i0 - 1) : T(2) * p0 - p1;
-                    p2 = i0 + 2 < G.n_k ? Yz(i0 + 2) : T(2) * p1 - p0;
+                i0 = max(0, min(i0, G.n_k - 2));
+                tt[u] = (T)(sv - i0);
+                lo[u] = i0 == 0;
+                hi[u] = i0 == G.n_k - 2;
+                const unsigned o = row + (unsigned)max(0, min(i0 - 1, G.n_k - 4)) * (unsigned)sizeof(T);
+                __builtin_memcpy(&ya[u], Y0 + o, sizeof(Q4));
+                __builtin_memcpy(&yb[u], Y1 + o, sizeof(Q4));
+                if (!LINZ) {
+                    __builtin_memcpy(&ma[u], M0 + o, sizeof(Q4));
+                    __builtin_memcpy(&mb[u], M1 + o, sizeof(Q4));
                 }
-                const T mk0 = T(0.5) * (p1 - pm), mk1 = T(0.5) * (p2 - p0);
-                const T t2 = tt * tt, t3 = t2 * tt;
-                const T lp = (T(2) * t3 - T(3) * t2 + T(1)) * p0 + (t3 - T(2) * t2 + tt) * mk0 +
-                             (T(-2) * t3 + T(3) * t2) * p1 + (t3 - t2) * mk1;
-                P = exp10_of<T>(lp);
             }
-            Pl[t * LB + b] = P;
+#pragma unroll
+            for (int u = 0; u < UL; ++u) {
+                T v[4];                                 // log10 P at z_j in the four columns
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    v[e] = c0 * ya[u].v[e] + c1 * yb[u].v[e];
+                    if (!LINZ) v[e] = v[e] + c2 * ma[u].v[e] + c3 * mb[u].v[e];
+                }
+                const T p0 = lo[u] ? v[0] : hi[u] ? v[2] : v[1], p1 = lo[u] ? v[1] : hi[u] ? v[3] : v[2];
+                const T pm = lo[u] ? T(2) * p0 - p1 : hi[u] ? v[1] : v[0];
+                const T p2 = hi[u] ? T(2) * p1 - p0 : lo[u] ? v[2] : v[3];
+                const T mk0 = T(0.5) * (p1 - pm), mk1 = T(0.5) * (p2 - p0);
+                const T t1 = tt[u], t2 = t1 * t1, t3 = t2 * t1;
+                const T lp = (T(2) * t3 - T(3) * t2 + T(1)) * p0 + (t3 - T(2) * t2 + t1) * mk0 +
+                             (T(-2) * t3 + T(3) * t2) * p1 + (t3 - t2) * mk1;
+                Pt[b0 + u] = in[u] ? exp10_of<T>(lp) : T(0);
+            }
         }
+        if (t < npr) scale[t] = make_double2(si * sj, ni * nj);
         __syncthreads();
         if (worker) {
             const int j0 = sg * len, j1 = min(min(256, na - c * 256), (sg + 1) * len);
-            const T* Wi = Ws + bi * WS;
-            const T* Wj = Ws + bj * WS;
             for (int jl = j0; jl < j1; ++jl) {
-                const T A = Wi[jl] * Wj[jl];
-                const T* Pj = Pl + jl * LB;
+                const T* Pj = Pl + jl * LB + sg * 4;
+                T A[PG];
 #pragma unroll
-                for (int e = 0; e < LB; ++e) acc[e] += A * Pj[e];
+                for (int q = 0; q < PG; ++q) A[q] = Ws[bi[q] * WS + jl] * Ws[bj[q] * WS + jl];
+#pragma unroll
+                for (int e = 0; e < LB; ++e) {
+                    const T P = Pj[e];
+#pragma unroll
+                    for (int q = 0; q < PG; ++q) acc[q][e] += A[q] * P;
+                }
             }
         }
         __syncthreads();
     }
     // segments -> LDS (nseg npr <= 256 rows of LB), added in order; with
     // several chunks the chunk's sums go to `part` for limber_reduce_kernel
-    if (worker)
+    if (worker) {
+        T* o = Pl + (sg * npr + pw) * LB;
 #pragma unroll
-        for (int e = 0; e < LB; ++e) Pl[(sg * npr + pw) * LB + e] = acc[e];
+        for (int q = 0; q < PG; ++q)
+            if (pw + q < npr)
+#pragma unroll
+                for (int e = 0; e < LB; ++e) o[q * LB + e] = acc[q][e];
+    }
     __syncthreads();
-    const int nout = npr * nl;
-    for (int o = t; o < nout; o += 256) {
-        const int p = o / nl, b = o % nl;
+    for (int e = t; e < npr * LB; e += 256) {
+        const int p = e / LB, b = e % LB;
+        if (b >= nl) continue;
         T v = T(0);
-        for (int s = 0; s < nseg; ++s) v += Pl[(s * npr + p) * LB + b];
+        for (int s = 0; s < nseg; ++s) v += Pl[s * npr * LB + e];
         if (nch > 1) {
-            part[(w * nch + c) * nout + o] = (double)v;
+            part[(w * nch + c) * npr * nl + p * nl + b] = (double)v;
             continue;
         }
-        int ci, cj;
-        pair_of(p, ci, cj);
-        const double mi = phys(9 + 2 * nb + ci), mj = phys(9 + 2 * nb + cj);
-        Cout[w * nout + o] = (1.0 + mi) * (1.0 + mj) * (double)v / (norm_in[w * nb + ci] * norm_in[w * nb + cj]);
+        const double2 f = scale[p];
+        Cout[w * npr * nl + p * nl + b] = f.x * (double)v / f.y;
     }
 }
 
 // Sum of the node chunks' Limber partial sums in chunk order, times
 // (1 + m_i)(1 + m_j) / (N_i N_j); one thread per (walker, spectrum, multipole).
-__global__ void limber_reduce_kernel(const double* __restrict__ theta, int64_t ld, int64_t B, ShearGeom G,
-                                     const int* __restrict__ pidx, const double* __restrict__ pfix,
-                                     const double* __restrict__ norm_in, const double* __restrict__ part,
+__global__ void limber_reduce_kernel(int64_t B, ShearGeom G, const double* __restrict__ norm_in, const double* __restrict__ part,
                                      double* __restrict__ Cout, const int* __restrict__ count) {
     if (count) B = min<int64_t>(B, *count);
     const int nb = G.n_bins, nl = G.n_ell, nout = G.n_pairs * nl, nch = (G.n_a + 255) / 256;
@@ -532,9 +562,8 @@ __global__ void limber_reduce_kernel(const double* __restrict__ theta, int64_t l
     int ci = 0, rem = p;
     while (rem >= nb - ci) { rem -= nb - ci; ++ci; }
     const int cj = ci + rem;
-    auto phys = [&](int slot) { const int ix = pidx[slot]; return ix >= 0 ? theta[w * ld + ix] : pfix[slot]; };
-    const double mi = phys(9 + 2 * nb + ci), mj = phys(9 + 2 * nb + cj);
-    Cout[w * nout + o] = (1.0 + mi) * (1.0 + mj) * v / (norm_in[w * nb + ci] * norm_in[w * nb + cj]);
+    const double* nm = norm_in + w * 2 * nb;
+    Cout[w * nout + o] = nm[nb + ci] * nm[nb + cj] * v / (nm[ci] * nm[cj]);
 }
 
 // ---------------------------------------------------------------- dense chi^2
@@ -730,24 +759,25 @@ static size_t windows_smem(const ns_model* m) { return 6 * 64 * (size_t)((m->n_a
 static int limber_lb(const ns_model* m) { return m->n_ell <= 20 ? 20 : 32; }
 
 static size_t limber_sum_smem(const ns_model* m, size_t elem) {
-    return ((size_t)m->n_bins * 257 + 256 * (size_t)limber_lb(m)) * elem;
+    const int nseg = std::max(1, 256 / m->n_pairs);
+    return (((size_t)m->n_bins * 257 + 3) / 4 * 4 + 256 * (size_t)limber_lb(m) + 4 * (size_t)nseg) * elem +
+           m->n_pairs * sizeof(double2);
 }
 
 template <class T, bool LINZ>
-static void launch_limber_sum(ns_model* m, const ShearGeom& G, const double* theta, int64_t ld, int64_t B,
+static void launch_limber_sum(ns_model* m, const ShearGeom& G, int64_t B,
                               const void* Mtab, const T* Win, const double* lchi, const double* norm, double* Cv,
                               double* part, const int* count, size_t sm, hipStream_t s) {
     const int nch = (m->n_a + 255) / 256;
     auto kern = limber_lb(m) == 20 ? limber_sum_kernel<T, LINZ, 20> : limber_sum_kernel<T, LINZ, 32>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)B, (unsigned)nch), dim3(256), sm, s, theta, ld, B, G,
-                       m->pidx_d.as<int>(), m->pfix_d.as<double>(), m->zsp_idx_d.as<int>(),
+    hipLaunchKernelGGL(kern, dim3((unsigned)B, (unsigned)nch), dim3(256), sm, s, B, G, m->zsp_idx_d.as<int>(),
                        m->zsp_coef_d.as<double>(), m->lell_d.as<double>(), m->ws_out.as<T>(), (const T*)Mtab, Win,
                        lchi, norm, Cv, part, count);
     NS_HIP(hipGetLastError());
     if (nch > 1) {
         const int64_t n = B * m->n_data;
-        hipLaunchKernelGGL(limber_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, theta, ld, B, G,
-                           m->pidx_d.as<int>(), m->pfix_d.as<double>(), norm, part, Cv, count);
+        hipLaunchKernelGGL(limber_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, B, G, norm,
+                           part, Cv, count);
         NS_HIP(hipGetLastError());
     }
 }
@@ -757,15 +787,15 @@ static void launch_limber(ns_model* m, const double* theta, int64_t ld, int64_t 
                           const int* count, hipStream_t s) {
     const ShearGeom G = shear_geom(m);
     const int na = m->n_a, nb = m->n_bins;
-    // windows [B][nb][na] (T), log10 chi [B][na], normalisations [B][nb], and
+    // windows [B][nb][na] (T), log10 chi [B][na], normalisations and 1 + m_i [B][2][nb], and
     // the Limber sums of each node chunk [B][nch][n_data]
     const size_t nch = (na + 255) / 256;
     const size_t wbytes = ((size_t)B * nb * na * sizeof(T) + 7) / 8 * 8;
-    m->ws_win.ensure(wbytes + (size_t)B * (na + nb + (nch > 1 ? nch * m->n_data : 0)) * sizeof(double));
+    m->ws_win.ensure(wbytes + (size_t)B * (na + 2 * nb + (nch > 1 ? nch * m->n_data : 0)) * sizeof(double));
     T* Win = m->ws_win.as<T>();
     double* lchi = reinterpret_cast<double*>(m->ws_win.as<char>() + wbytes);
     double* norm = lchi + (size_t)B * na;
-    double* part = norm + (size_t)B * nb;
+    double* part = norm + (size_t)B * 2 * nb;
     const size_t sm1 = windows_smem(m), sm2 = limber_sum_smem(m, sizeof(T));
     NS_CHECK(sm1 <= 160 * 1024 && sm2 <= 160 * 1024, NS_E_UNSUPPORTED, "Limber stage needs more LDS than a workgroup has");
     {
@@ -782,9 +812,9 @@ static void launch_limber(ns_model* m, const double* theta, int64_t ld, int64_t 
     }
     TraceScope ts(m, s, "limber");
     if (m->z_linear)
-        launch_limber_sum<T, true>(m, G, theta, ld, B, Mtab, Win, lchi, norm, Cv, part, count, sm2, s);
+        launch_limber_sum<T, true>(m, G, B, Mtab, Win, lchi, norm, Cv, part, count, sm2, s);
     else
-        launch_limber_sum<T, false>(m, G, theta, ld, B, Mtab, Win, lchi, norm, Cv, part, count, sm2, s);
+        launch_limber_sum<T, false>(m, G, B, Mtab, Win, lchi, norm, Cv, part, count, sm2, s);
 }
 
 double* shear_spectra_from_table(ns_model* m, const double* theta, int64_t ld, int64_t B, int prec,
