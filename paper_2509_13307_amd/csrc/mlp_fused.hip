@@ -25,6 +25,8 @@
 #include "devutil.h"
 #include "nsmi.h"
 
+#include <type_traits>
+
 namespace nsmi {
 
 constexpr int FM_MAXHID = 6;   // hidden GEMM layers supported
@@ -38,11 +40,9 @@ struct FusedNet {
     const float* vec;      // hidden layer l: b, beta, gamma at l 3H + {0, H, 2H}; output bias after them
     const float* mu; const float* sigma;
     float* out; int is_log;
-    float* t;              // pre-activations of hidden layer l + 1 at l tslot, [rows x H] (SAVE)
 };
 
 struct FusedArgs {
-    int64_t tslot;
     FusedNet net[4];
     int n_hidden;        // hidden GEMM layers (network layers - 2)
     int n_in, N_out, mu_rows;
@@ -59,6 +59,13 @@ struct FusedArgs {
     const double* theta_s; int64_t ld_s; int d;   // support check of each walker
     const int* pk; const double* pa; const double* pb;
 };
+// the forward of a gradient: also each network's pre-activations, of hidden
+// layer l + 1 at l tslot, [rows x H] (apart, as the others' launches would carry them)
+struct FusedSave : FusedArgs {
+    float* t[4];
+    int64_t tslot;
+};
+template <bool SAVE> using FusedKernelArgs = std::conditional_t<SAVE, FusedSave, FusedArgs>;
 
 // One chi^2 term of output c with model value y (the FP32 output the store
 // path would write): diagonal Gaussian ((data - y) / sigma)^2, or the
@@ -117,7 +124,7 @@ bool fused_shape(const std::vector<int>& dims) {
 template <int H, int RT, bool X3, int P, int CT, bool CHI, bool SAVE>
 __global__ __launch_bounds__(2 * H / CT) void mlp_fused_kernel(
     const double* __restrict__ theta, int64_t ld, int64_t rows, int rows_per_walker, const int* __restrict__ src,
-    const double* __restrict__ fix, const double* __restrict__ znodes, FusedArgs A, const int* __restrict__ count) {
+    const double* __restrict__ fix, const double* __restrict__ znodes, FusedKernelArgs<SAVE> A, const int* __restrict__ count) {
     constexpr int WC = 32 * CT;            // output units per wave and column block
     constexpr int NT = 64 * (H / WC);      // threads: one wave per WC units
     constexpr int R = 32 * RT;             // rows per workgroup
@@ -221,7 +228,8 @@ __global__ __launch_bounds__(2 * H / CT) void mlp_fused_kernel(
 #pragma unroll
             for (int j = 0; j < FU; ++j) {
                 const int rr = rr0 + (j0 + j) * RS;
-                if (SAVE && rr < nvalid) N.t[(r0 + rr) * H + c] = acc[j];
+                if constexpr (SAVE)
+                    if (rr < nvalid) A.t[g][(r0 + rr) * H + c] = acc[j];
                 const float v = gated<float>(acc[j], be1, ga1);
                 const uint16_t hi = f2bf(v);
                 hs[rr * HS + c] = hi;
@@ -384,8 +392,8 @@ __global__ __launch_bounds__(2 * H / CT) void mlp_fused_kernel(
     // epilogue of hidden segment v: gated activation of this wave's units, the
     // BF16 (hi, lo) split into LDS
     auto hidden_epi = [&]() {
-        if (SAVE) {
-            float* tb = N.t + (v + 1) * A.tslot + r0 * H;
+        if constexpr (SAVE) {
+            float* tb = A.t[g] + (v + 1) * A.tslot + r0 * H;
 #pragma unroll
             for (int j = 0; j < CT; ++j) {
                 const unsigned lofs = (unsigned)((lane >> 5) * 4 * H + wave * WC + j * 32 + (lane & 31));
@@ -574,7 +582,7 @@ __global__ __launch_bounds__(256) void chi2_fused_finish_kernel(const double* __
 }
 
 template <int H, int RT, bool X3, int P, int CT, bool CHI, bool SAVE = false>
-static void launch_fused(ns_model* m, const FusedArgs& A, const double* theta, int64_t ld, int64_t rows, int rpw,
+static void launch_fused(ns_model* m, const FusedSave& A, const double* theta, int64_t ld, int64_t rows, int rpw,
                          int G, const int* count, hipStream_t s) {
     constexpr int R = 32 * RT;
     constexpr int NT = 64 * (H / (32 * CT));
@@ -586,7 +594,8 @@ static void launch_fused(ns_model* m, const FusedArgs& A, const double* theta, i
         NS_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
     const dim3 grid((unsigned)((rows + R - 1) / R), (unsigned)G, (unsigned)A.qg);
     hipLaunchKernelGGL(kern, grid, dim3(NT), smem, s, theta, ld, rows, rpw, m->emu_src_d.as<int>(),
-                       m->emu_fix_d.as<double>(), m->znodes_d.as<double>(), A, count);
+                       m->emu_fix_d.as<double>(), m->znodes_d.as<double>(),
+                       static_cast<const FusedKernelArgs<SAVE>&>(A), count);
 }
 
 // Candidate launch shapes: 64-row blocks with waves of 32 or 64 output units
@@ -598,7 +607,7 @@ static void launch_fused(ns_model* m, const FusedArgs& A, const double* theta, i
 // more workgroups and a shorter serial chain per workgroup, at the price of
 // the hidden layers computed once per column block.  All candidates give
 // identical results.
-using FusedLaunch = void (*)(ns_model*, const FusedArgs&, const double*, int64_t, int64_t, int, int, const int*,
+using FusedLaunch = void (*)(ns_model*, const FusedSave&, const double*, int64_t, int64_t, int, int, const int*,
                              hipStream_t);
 // fn_save (nullptr where the hidden layers run once per output block, which
 // would store the pre-activations as often): the launch for a gradient, which
@@ -670,10 +679,10 @@ int fused_ncfg_of(int h512, int x3) { return fused_ncfg(h512, x3); }
 // ordered weights (shape outside fused_shape) or the form is not BF16-operand.
 // Shared by the store and chi^2 modes: the one-kernel arguments of networks
 // nets[0..G) (outputs and flags filled in by the caller).
-static FusedArgs fused_args(ns_model* m, const int* nets, int G) {
+static FusedSave fused_args(ns_model* m, const int* nets, int G) {
     const Net& n0 = *m->nets[nets[0]];
     const int L = n0.n_layers;
-    FusedArgs A{};
+    FusedSave A{};
     A.n_hidden = L - 2;
     A.n_in = n0.dims[0];
     A.N_out = n0.dims[L];
@@ -698,7 +707,7 @@ static FusedArgs fused_args(ns_model* m, const int* nets, int G) {
 // outside stream capture and tracing, or pinned / read from the cache), then
 // the launch; in chi^2 mode with the output blocks split over workgroups, the
 // finishing sum of the tile partials.
-static void fused_run(ns_model* m, const FusedArgs& A, int H, bool x3, int G, const double* theta, int64_t ld,
+static void fused_run(ns_model* m, const FusedSave& A, int H, bool x3, int G, const double* theta, int64_t ld,
                       int64_t B, const int* count, hipStream_t s) {
     const Net& n0 = *m->nets[0];
     const int rpw = n0.out_mu_rows;
@@ -709,7 +718,7 @@ static void fused_run(ns_model* m, const FusedArgs& A, int H, bool x3, int G, co
     // candidate c with its output-block grouping, on `nr` rows given on the
     // host (tuning) or on the launch's rows and device count
     auto run_rows = [&](int c, int64_t nr, const int* cnt) {
-        FusedArgs Ac = A;
+        FusedSave Ac = A;
         Ac.qg = cfgs[c].split_out ? ncb : 1;
         (Ac.chi ? cfgs[c].fn_chi : Ac.tslot ? cfgs[c].fn_save : cfgs[c].fn)(m, Ac, theta, ld, nr, rpw, G, cnt, s);
         if (Ac.chi && Ac.qg > 1)
@@ -794,11 +803,11 @@ bool emulator_forward_fused(ns_model* m, const int* nets, int G, const double* t
     if (prec != NS_BF16 && prec != NS_BF16X3) return false;
     const Net& n0 = *m->nets[nets[0]];
     if (!n0.fused) return false;
-    FusedArgs A = fused_args(m, nets, G);
+    FusedSave A = fused_args(m, nets, G);
     A.ldo = ldo;
     A.tslot = tsave ? (int64_t)slot_stride : 0;
     for (int g = 0; g < G; ++g) {
-        A.net[g].t = tsave ? tsave + g * net_stride : nullptr;
+        A.t[g] = tsave ? tsave + g * net_stride : nullptr;
         A.net[g].out = static_cast<float*>(outs[g]);
         A.net[g].is_log = is_log[g];
     }
@@ -831,7 +840,7 @@ bool emulator_chi2_fused(ns_model* m, const double* theta, int64_t ld, int64_t B
     const int id0 = 0;
     const Net& n0 = *m->nets[0];
     const int H = n0.dims[1];
-    FusedArgs A = fused_args(m, &id0, 1);
+    FusedSave A = fused_args(m, &id0, 1);
     const bool cv = m->kind == NS_MODEL_CMB_CV;
     A.net[0].out = nullptr;
     A.net[0].is_log = cv ? 0 : m->spec_log[0];             // the cosmic-variance terms take log10 C_l
