@@ -375,38 +375,41 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(Group<Epi> G, int64_t ld
 }
 
 // ------------------------------------------------------ MFMA GEMM, FP32
-// Same WG tiling; v_mfma_f32_32x32x2f32, BK = 32, LDS row stride 33 floats.
+// Tiles of 64 TI x 64 TI, four waves of TI x TI MFMA tiles; v_mfma_f32_32x32x2f32,
+// BK = 32, LDS row stride 33 floats.  (Two LDS buffers and one barrier per K
+// block: 1.5% slower at 4096 rows, 67 KB holding two workgroups per CU.)
 constexpr int GF_K = 32, GF_LDS = GF_K + 1;
 
-template <class Epi>
+template <class Epi, int TI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(Group<Epi> G, int64_t lda, int64_t M, int N, int K,
                                                        const int* __restrict__ count, int rows_per_count) {
-    __shared__ float As[GB_M * GF_LDS];
-    __shared__ float Bs[GB_N * GF_LDS];
+    constexpr int BM = 64 * TI, LD = 2 * TI;           // tile edge; float4 chunks per thread and operand
+    __shared__ float As[BM * GF_LDS];
+    __shared__ float Bs[BM * GF_LDS];
     const int g = blockIdx.z;
     const float* A = static_cast<const float*>(G.A[g]);
     const float* W = static_cast<const float*>(G.W[g]);
     const Epi& epi = G.epi[g];
     if (count) M = min<int64_t>(M, (int64_t)(*count) * rows_per_count);
-    const int64_t m0 = (int64_t)blockIdx.y * GB_M;
-    const int n0 = blockIdx.x * GB_N;
+    const int64_t m0 = (int64_t)blockIdx.y * BM;
+    const int n0 = blockIdx.x * BM;
     if (m0 >= M) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wr = wave >> 1, wc = wave & 1;
-    f32x16_t acc[2][2];
+    f32x16_t acc[TI][TI];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < TI; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-    // 128 rows x 32 k = 1024 float4 chunks per operand; the next K block is
+    // BM rows x 32 k = 8 BM float4 chunks per operand; the next K block is
     // fetched into registers while the current one feeds the MFMAs
-    float4 ra[4], rb[4];
+    float4 ra[LD], rb[LD];
     auto gload = [&](int k0) {
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
+        for (int it = 0; it < LD; ++it) {
             const int c = tid + it * 256;
             const int row = c >> 3, kc = (c & 7) * 4;
             const int64_t gr = m0 + row;
@@ -420,7 +423,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(Group<Epi> G, int64_t lda
     gload(0);
     for (int k0 = 0; k0 < K; k0 += GF_K) {
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
+        for (int it = 0; it < LD; ++it) {
             const int c = tid + it * 256;
             const int row = c >> 3, kc = (c & 7) * 4;
             float* ad = &As[row * GF_LDS + kc];
@@ -433,29 +436,29 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(Group<Epi> G, int64_t lda
 #pragma unroll
         for (int kk = 0; kk < GF_K; kk += 2) {
             const int koff = kk + (lane >> 5);
-            float a[2], b[2];
+            float a[TI], b[TI];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) a[i] = As[(wr * 64 + i * 32 + (lane & 31)) * GF_LDS + koff];
+            for (int i = 0; i < TI; ++i) a[i] = As[(wr * 32 * TI + i * 32 + (lane & 31)) * GF_LDS + koff];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) b[j] = Bs[(wc * 64 + j * 32 + (lane & 31)) * GF_LDS + koff];
+            for (int j = 0; j < TI; ++j) b[j] = Bs[(wc * 32 * TI + j * 32 + (lane & 31)) * GF_LDS + koff];
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < TI; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < TI; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int c = n0 + wc * 64 + j * 32 + (lane & 31);
+    for (int j = 0; j < TI; ++j) {
+        const int c = n0 + wc * 32 * TI + j * 32 + (lane & 31);
         if (c >= N) continue;
         const auto p = epi.col(c);
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < TI; ++i)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int64_t row = m0 + wr * 64 + i * 32 + (lane >> 5) * 4 + (r >> 2) * 8 + (r & 3);
+                const int64_t row = m0 + wr * 32 * TI + i * 32 + (lane >> 5) * 4 + (r >> 2) * 8 + (r & 3);
                 if (row < M) epi.store(row, c, p, acc[i][j][r]);
             }
     }
@@ -753,6 +756,22 @@ static inline dim3 grid3(int64_t M, int N, int bm, int bn, int G) {
     return dim3((unsigned)((N + bn - 1) / bn), (unsigned)((M + bm - 1) / bm), (unsigned)G);
 }
 
+// FP32 GEMM launch: 128 x 128 tiles where they give every CU two workgroups,
+// 64 x 64 ones below (one K order, the same results).  Gradients of four
+// networks of 2 500 outputs, whole call, 128 / 64: 64 rows 541 / 280 us, 1000
+// 537 / 337, 2000 675 / 583, 2500 956 / 716, 4096 (two each) 1033 / 1069; the
+// FP32 value of 300 rows 230 / 125, of 4096 710 / 725.
+template <class Epi>
+static void launch_gemm_f32(const ns_model* m, const Group<Epi>& P, int64_t rows, int N, int K, int G,
+                            const int* count, int rpw, hipStream_t s) {
+    const dim3 big = grid3(rows, N, 128, 128, G);
+    if ((int64_t)big.x * big.y * G < 2 * (int64_t)device_cus(m->device))
+        hipLaunchKernelGGL((gemm_f32_kernel<Epi, 1>), grid3(rows, N, 64, 64, G), dim3(256), 0, s, P, (int64_t)K, rows,
+                           N, K, count, rpw);
+    else
+        hipLaunchKernelGGL((gemm_f32_kernel<Epi, 2>), big, dim3(256), 0, s, P, (int64_t)K, rows, N, K, count, rpw);
+}
+
 // Compute units of device dev (queried once per device).
 int device_cus(int dev) {
     static int cus[64] = {0};
@@ -909,7 +928,6 @@ void emulator_forward(ns_model* m, const int* nets, int G, const double* theta, 
             }
         } else if (prec == NS_FP32) {
             NS_CHECK(K % GF_K == 0, NS_E_UNSUPPORTED, "FP32 MFMA layers need K % 32 == 0");
-            const dim3 gr = grid3(rows, N, GB_M, GB_N, G);
             if (!last) {
                 Group<EpiHidden<float, float>> P{};
                 for (int g = 0; g < G; ++g) {
@@ -918,8 +936,7 @@ void emulator_forward(ns_model* m, const int* nets, int G, const double* theta, 
                     P.epi[g] = {ly.b32.as<float>(), ly.beta32.as<float>(), ly.gamma32.as<float>(), (float*)D_of(g),
                                 (int64_t)N, (float*)tslot(g, l)};
                 }
-                hipLaunchKernelGGL((gemm_f32_kernel<EpiHidden<float, float>>), gr, dim3(256), 0, s, P, (int64_t)K,
-                                   rows, N, K, count, rpw);
+                launch_gemm_f32(m, P, rows, N, K, G, count, rpw, s);
             } else {
                 Group<EpiOut<float>> P{};
                 for (int g = 0; g < G; ++g) {
@@ -929,8 +946,7 @@ void emulator_forward(ns_model* m, const int* nets, int G, const double* theta, 
                     P.epi[g] = {ly.b32.as<float>(), net.out_mu32.as<float>(), net.out_sigma32.as<float>(),
                                 (float*)D_of(g), ldo, net.out_mu_rows, N, is_log[g]};
                 }
-                hipLaunchKernelGGL((gemm_f32_kernel<EpiOut<float>>), gr, dim3(256), 0, s, P, (int64_t)K, rows, N, K,
-                                   count, rpw);
+                launch_gemm_f32(m, P, rows, N, K, G, count, rpw, s);
             }
         } else {
             NS_CHECK(K % GB_K == 0, NS_E_UNSUPPORTED, "BF16 MFMA layers need K % 64 == 0");
@@ -1075,8 +1091,7 @@ static void backward_impl(ns_model* m, const int* nets, int G, int64_t B, const 
             else
                 launch_gemm_f64(m, P, (int64_t)Kred, rows, Nout, Kred, G, count, rpw, s);
         } else
-            hipLaunchKernelGGL((gemm_f32_kernel<EpiBack<T>>), grid3(rows, Nout, GB_M, GB_N, G), dim3(256), 0, s, P,
-                               (int64_t)Kred, rows, Nout, Kred, count, rpw);
+            launch_gemm_f32(m, P, rows, Nout, Kred, G, count, rpw, s);
         NS_HIP(hipGetLastError());
         cur ^= 1;
     }
