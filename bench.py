@@ -21,6 +21,7 @@ import time
 import numpy as np
 
 MI355X_PEAK = {"bf16": 2500.0, "bf16x3": 2500.0, "fp32": 157.3, "fp64": 78.6}   # dense TFLOP/s
+INT8_PEAK = 5000.0          # TOP/s, dense
 HBM_PEAK_GBS = 8000.0
 
 
@@ -86,7 +87,12 @@ def roofline_of(dom, avg_s, prec, m, B, workload):
     K_last, N_last = net["W"][-1].shape[1], net["W"][-1].shape[0]
     K_hid = net["W"][1].shape[1]
     issued = None
-    if dom.startswith("mlp_fused"):
+    peak_of = MI355X_PEAK[prec]
+    if dom.startswith("mlp_i8"):
+        # FP64 layers as 28 int8 products of 7 digits each: the FP64 work against the int8 peak / 28
+        work, unit, bound = n_nets * mlp_flops(net, rows), "TFLOP/s", "mfma"
+        peak_of = round(INT8_PEAK / 28, 1)
+    elif dom.startswith("mlp_fused"):
         work = n_nets * mlp_flops(net, rows)
         gemm = n_nets * sum(2.0 * rows * W.shape[0] * W.shape[1] for W in net["W"][1:])
         # MFMA instructions issued: 3 products per split-BF16 multiply
@@ -101,7 +107,7 @@ def roofline_of(dom, avg_s, prec, m, B, workload):
         work, unit, bound = float(B) * m["data"].size * elem, "GB/s", "hbm"
     if unit == "TFLOP/s":
         achieved = work / avg_s / 1e12
-        peak = MI355X_PEAK[prec]
+        peak = peak_of
     else:
         achieved = work / avg_s / 1e9
         peak = HBM_PEAK_GBS
@@ -377,6 +383,8 @@ def adjoint_leg(Model, W, torch, dev):
             tr = g.trace_report()
             g.trace(False)
             key = "adj_gemm_f64" if prec == "fp64" else "adj_gemm_f32"
+            if prec == "fp64" and "mlp_i8_f64_adjoint" in tr:   # wide networks: all layers in one kernel
+                key = "mlp_i8_f64_adjoint"
             n_adj, t_adj = tr.get(key, (0, 0.0))
             peak = MI355X_PEAK["fp64" if prec == "fp64" else "fp32"]
             achieved = back_flops / (t_adj * 1e-3) / 1e12 if t_adj > 0 else None

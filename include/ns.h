@@ -64,7 +64,9 @@ typedef enum {
  * chi^2 (Cholesky whitening, reductions) and all sampler bookkeeping are FP64
  * in every form. */
 typedef enum {
-    NS_FP64 = 0,   /* everything in double                                   */
+    NS_FP64 = 0,   /* everything in double; layers of networks whose hidden  */
+                   /* widths are all >= 256 as exact sums of int8 digit      */
+                   /* products (error below that of a product in double)     */
     NS_FP32 = 1,   /* emulator and Limber stages in float                    */
     NS_BF16 = 2,   /* hidden and output layers on BF16 MFMA, FP32 accumulate;
                       first layer, output transform and Limber in FP32       */
