@@ -38,3 +38,26 @@ def test_spectra_at_kernel_edges(n_k, n_bins, n_a, n_ell, z_interp, n_z, prec, t
     err = np.max(np.abs(got.reshape(ref.shape) - ref) / np.max(np.abs(ref), axis=1, keepdims=True))
     print(f"  max error {err:.2e}", flush=True)
     assert err < tol
+
+
+@pytest.mark.parametrize("B", [1, 31, 33, 65])
+def test_support_of_every_coordinate(B):
+    """The dense likelihood's support test, eight lanes per walker: a coordinate
+    outside its uniform prior gives -inf for that walker alone, a NaN does not."""
+    print(f"case dense support B={B}", flush=True)
+    from paper_2509_13307_amd import Model
+    m = W.load_model("shear10")
+    g = Model(m)
+    base = np.repeat(m["theta_fid"][None], B, axis=0)
+    ref = g.loglike(torch.tensor(base, device=DEV)).cpu().numpy()
+    assert np.all(np.isfinite(ref))
+    for j in range(m["d"]):
+        if m["prior_kind"][j] != 0:
+            continue
+        th = base.copy()
+        r = (7 * j + 3) % B
+        th[r, j] = m["prior_b"][j] + 1e-6 * (m["prior_b"][j] - m["prior_a"][j])
+        got = g.loglike(torch.tensor(th, device=DEV)).cpu().numpy()
+        assert got[r] == -np.inf
+        np.testing.assert_array_equal(np.delete(got, r), np.delete(ref, r))
+    g.close()
