@@ -1001,7 +1001,7 @@ void emulator_forward(ns_model* m, const int* nets, int G, const double* theta, 
 // lane & 15, units 4 (lane >> 4) + i of the block in the i-th product), their
 // sums added in LDS (n1, a hidden width, is a multiple of 64).  Bound by reading delta; one wave per row, which read all
 // of W_1 and reduced every input over the wave, took 145 us at 32768 rows of
-// 512 units, where delta alone needs 27 us at the rate of a large copy.
+// 512 units, now 30, where delta alone needs 27 us at the rate of a large copy.
 template <class T>
 __global__ __launch_bounds__(256) void first_layer_back_kernel(const T* __restrict__ delta, int64_t rows,
                                                                int n1, int n_in, FirstArgs<T, T> P, size_t dstride,
