@@ -139,7 +139,25 @@ static bool digit_weights_even(const ns_net_desc& nd) {
     return true;
 }
 
-static Net* build_net(const ns_net_desc& nd, int mu_rows) {
+// Whether the model's FP64 layers run on digits: one answer for all its
+// networks, because they are launched as one group, whose kernels read every
+// network's digit tiles.  (A description that build_net will refuse: false.)
+static bool digits_admitted(const ns_model_desc* D) {
+    if (!D->nets || D->n_nets < 1) return false;
+    for (int i = 0; i < D->n_nets; ++i) {
+        const ns_net_desc& nd = D->nets[i];
+        if (nd.n_layers < 2 || !nd.dims || !nd.W) return false;
+        const std::vector<int> dims(nd.dims, nd.dims + nd.n_layers + 1);
+        for (int v : dims)
+            if (v < 1) return false;
+        for (int l = 0; l < nd.n_layers; ++l)
+            if (!nd.W[l]) return false;
+        if (!digit_shape(dims) || !digit_weights_even(nd)) return false;
+    }
+    return true;
+}
+
+static Net* build_net(const ns_net_desc& nd, int mu_rows, bool digits) {
     NS_CHECK(nd.n_layers >= 2, NS_E_SHAPE, "emulator needs >= 2 layers");
     check_ptr(nd.dims, "net.dims");
     check_ptr(nd.W, "net.W");
@@ -248,7 +266,7 @@ static Net* build_net(const ns_net_desc& nd, int mu_rows) {
                 upload(ly->gamma32, ga.data(), (size_t)N);
             }
         }
-        net->digits = digit_shape(net->dims) && digit_weights_even(nd);
+        net->digits = digits;
         if (net->digits)
             for (int l = 1; l < nd.n_layers; ++l) {
                 Layer* ly = net->layers[l];
@@ -342,7 +360,8 @@ static void build_model(ns_model* m, const ns_model_desc* D) {
     NS_CHECK(D->n_nets == want_nets, NS_E_SHAPE, "wrong number of emulator networks for this model kind");
     const int mu_rows = D->kind == NS_MODEL_SHEAR ? D->n_z : 1;
     NS_CHECK(mu_rows >= 1, NS_E_SHAPE, "n_z must be >= 1");
-    for (int i = 0; i < D->n_nets; ++i) m->nets.push_back(build_net(D->nets[i], mu_rows));
+    const bool digits = digits_admitted(D);
+    for (int i = 0; i < D->n_nets; ++i) m->nets.push_back(build_net(D->nets[i], mu_rows, digits));
     const int n_in = m->nets[0]->dims[0];
     for (auto* n : m->nets) NS_CHECK(n->dims[0] == n_in, NS_E_SHAPE, "networks must share their inputs");
     m->n_data = D->n_data;
@@ -855,5 +874,15 @@ ns_status ns_tuning_report(ns_model* model, char* buf, int64_t buf_len) {
 }
 
 const char* ns_last_error(void) { return g_last_error.c_str(); }
+
+// Not in the ABI's header: the host's decision alone, for tests without a GPU.
+int32_t nsmi_digits_admitted(const ns_model_desc* desc) {
+    int32_t yes = 0;
+    (void)guard([&] {
+        check_ptr(desc, "desc");
+        yes = digits_admitted(desc) ? 1 : 0;
+    });
+    return yes;
+}
 
 }  // extern "C"

@@ -617,6 +617,7 @@ static void launch_gemm_i8(ns_model* m, const Group<Epi>& P, int64_t rows, int N
     DigitRows R{};
     DigitGroup<Epi> D{};
     for (int g = 0; g < G; ++g) {
+        NS_CHECK(P.W[g] && P.Wl[g], NS_E_UNSUPPORTED, "network without digit tiles");
         R.A[g] = static_cast<const double*>(P.A[g]);
         R.tiles[g] = m->ws_digits.as<char>() + g * tile_bytes;
         R.back[g] = reinterpret_cast<double*>(m->ws_digits.as<char>() + G * tile_bytes + g * back_bytes);
@@ -840,8 +841,10 @@ void emulator_forward(ns_model* m, const int* nets, int G, const double* theta, 
                       hipStream_t s, bool save_t) {
     NS_CHECK(G >= 1 && G <= MAXG, NS_E_UNSUPPORTED, "at most 4 networks per launch");
     const Net& net0 = *m->nets[nets[0]];
-    for (int g = 1; g < G; ++g)
+    for (int g = 1; g < G; ++g) {
         NS_CHECK(m->nets[nets[g]]->dims == net0.dims, NS_E_SHAPE, "grouped networks must share their shapes");
+        NS_CHECK(m->nets[nets[g]]->digits == net0.digits, NS_E_UNSUPPORTED, "grouped networks must share their form");
+    }
     const int L = net0.n_layers;
     const int rpw = net0.out_mu_rows;                 // rows per walker
     const int64_t rows = B * rpw;

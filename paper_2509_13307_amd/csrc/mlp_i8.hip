@@ -517,6 +517,7 @@ bool emulator_forward_digits(ns_model* m, const int* nets, int G, const double* 
             DigitLayer& D = l < L - 1 ? N.hid[l - 1] : N.out;
             D.W = ly.Wd.as<i32x4_t>();
             D.back = ly.wback.as<double>();
+            NS_CHECK(D.W && D.back, NS_E_UNSUPPORTED, "network without digit tiles");
             D.b = ly.b64.as<double>();
             D.beta = ly.beta64.as<double>();
             D.gamma = ly.gamma64.as<double>();
@@ -563,6 +564,7 @@ bool emulator_backward_digits(ns_model* m, const int* nets, int G, int64_t B, co
             DigitLayer& D = l < L - 1 ? N.hid[l - 1] : N.out;
             D.W = ly.WTd.as<i32x4_t>();
             D.back = ly.wtback.as<double>();
+            NS_CHECK(D.W && D.back, NS_E_UNSUPPORTED, "network without digit tiles");
             D.beta = ly.beta64.as<double>();
             D.gamma = ly.gamma64.as<double>();
             D.t = l < L - 1 ? t + l * slot_stride : nullptr;

@@ -111,7 +111,7 @@ struct Net {
     // (kq NT + nt) 64, lane q holding W[16 nt + q % 16][4 kq + q / 16] (0 past N)
     bool narrow64 = false;
     DevBuf Wf64;
-    bool digits = false;                     // FP64 GEMM layers run on int8 digits
+    bool digits = false;                     // FP64 GEMM layers run on int8 digits (all networks of a model alike)
     ~Net();
 };
 

@@ -61,10 +61,21 @@ class Model:
     """
 
     def __init__(self, desc, device=0):
+        self.device = device
+        D = self._describe(desc)
+        # torch ships its own HIP runtime: it has to open the GPU before the
+        # library's runtime does, or torch finds no device afterwards.
+        torch.cuda.init()
+        h = ctypes.c_void_p()
+        C.check(C.lib().ns_model_create(ctypes.byref(D), device, ctypes.byref(h)))
+        self._h = h
+        self._keep = []          # the library copied everything it needs
+
+    def _describe(self, desc):
+        """The C description of ``desc``; the arrays that it points to stay in ``self._keep``."""
         self._keep = []
         self.kind = desc["kind"]
         self.d = int(desc["d"])
-        self.device = device
         self.n_data = 0
         D = C.ModelDesc()
         D.kind = C.KINDS[self.kind]
@@ -113,13 +124,7 @@ class Model:
                 D.z_interp = 1 if desc.get("z_interp", "cubic") == "linear" else 0
                 D.pidx = self._p(_i32(desc["pidx"]), C.c_int32_p)
                 D.pfix = self._p(_f64(desc["pfix"]), C.c_double_p)
-        # torch ships its own HIP runtime: it has to open the GPU before the
-        # library's runtime does, or torch finds no device afterwards.
-        torch.cuda.init()
-        h = ctypes.c_void_p()
-        C.check(C.lib().ns_model_create(ctypes.byref(D), device, ctypes.byref(h)))
-        self._h = h
-        self._keep = []          # the library copied everything it needs
+        return D
 
     def _p(self, a, typ):
         self._keep.append(a)
