@@ -64,9 +64,13 @@ typedef enum {
  * chi^2 (Cholesky whitening, reductions) and all sampler bookkeeping are FP64
  * in every form. */
 typedef enum {
-    NS_FP64 = 0,   /* everything in double; layers of networks whose hidden  */
-                   /* widths are all >= 256 as exact sums of int8 digit      */
-                   /* products (error below that of a product in double)     */
+    NS_FP64 = 0,   /* everything in double.  Layers of networks whose hidden */
+                   /* widths are all >= 256 and whose weights are of similar */
+                   /* size run as exact sums of int8 digit products, with an */
+                   /* absolute error relative to the row's largest entry     */
+                   /* times the unit's largest weight (over blocks of 512);  */
+                   /* rows of which that would exceed the error of products  */
+                   /* in double, and other networks, take those              */
     NS_FP32 = 1,   /* emulator and Limber stages in float                    */
     NS_BF16 = 2,   /* hidden and output layers on BF16 MFMA, FP32 accumulate;
                       first layer, output transform and Limber in FP32       */

@@ -101,63 +101,7 @@ static void check_ptr(const void* p, const char* what) {
     if (!p) throw Error{NS_E_INVALID, std::string("null pointer: ") + what};
 }
 
-// Weights that digits of a common scale hold as well as doubles do: within
-// every block of 512 inputs of a unit, and of 512 units of an input (the
-// adjoint's rows), the largest weight is at most 8 times the root mean square.
-// The digits' error goes with the largest weight and the FP64 product's with
-// the root mean square; for normal draws the former (largest / rms about 3.5)
-// is half the latter, so at 8 they are about equal.
-static bool digit_weights_even(const ns_net_desc& nd) {
-    constexpr int BLOCK = 512;
-    auto even = [](double mx, double ss, int n) {
-        return mx * mx * n <= 64.0 * ss && (mx == 0.0 || (mx > 1e-140 && mx < 1e140));
-    };
-    for (int l = 1; l < nd.n_layers; ++l) {
-        const int K = nd.dims[l], N = nd.dims[l + 1];
-        std::vector<double> cm(K, 0.0), cs(K, 0.0);
-        for (int n = 0; n < N; ++n) {
-            for (int k0 = 0; k0 < K; k0 += BLOCK) {
-                double mx = 0.0, ss = 0.0;
-                for (int k = k0; k < std::min(K, k0 + BLOCK); ++k) {
-                    const double v = std::fabs(nd.W[l][(size_t)n * K + k]);
-                    if (!std::isfinite(v)) return false;
-                    mx = std::max(mx, v);
-                    ss += v * v;
-                    cm[k] = std::max(cm[k], v);
-                    cs[k] += v * v;
-                }
-                if (!even(mx, ss, std::min(BLOCK, K - k0))) return false;
-            }
-            if ((n + 1) % BLOCK == 0 || n + 1 == N) {
-                for (int k = 0; k < K; ++k) {
-                    if (!even(cm[k], cs[k], n % BLOCK + 1)) return false;
-                    cm[k] = cs[k] = 0.0;
-                }
-            }
-        }
-    }
-    return true;
-}
-
-// Whether the model's FP64 layers run on digits: one answer for all its
-// networks, because they are launched as one group, whose kernels read every
-// network's digit tiles.  (A description that build_net will refuse: false.)
-static bool digits_admitted(const ns_model_desc* D) {
-    if (!D->nets || D->n_nets < 1) return false;
-    for (int i = 0; i < D->n_nets; ++i) {
-        const ns_net_desc& nd = D->nets[i];
-        if (nd.n_layers < 2 || !nd.dims || !nd.W) return false;
-        const std::vector<int> dims(nd.dims, nd.dims + nd.n_layers + 1);
-        for (int v : dims)
-            if (v < 1) return false;
-        for (int l = 0; l < nd.n_layers; ++l)
-            if (!nd.W[l]) return false;
-        if (!digit_shape(dims) || !digit_weights_even(nd)) return false;
-    }
-    return true;
-}
-
-static Net* build_net(const ns_net_desc& nd, int mu_rows, bool digits) {
+static Net* build_net(const ns_net_desc& nd, int mu_rows, const DigitPlan& plan, int index) {
     NS_CHECK(nd.n_layers >= 2, NS_E_SHAPE, "emulator needs >= 2 layers");
     check_ptr(nd.dims, "net.dims");
     check_ptr(nd.W, "net.W");
@@ -266,11 +210,16 @@ static Net* build_net(const ns_net_desc& nd, int mu_rows, bool digits) {
                 upload(ly->gamma32, ga.data(), (size_t)N);
             }
         }
-        net->digits = digits;
+        net->digits = plan.forward;
+        net->digits_back = plan.forward && plan.back;
+        net->digits_out = plan.forward && plan.out;
         if (net->digits)
             for (int l = 1; l < nd.n_layers; ++l) {
                 Layer* ly = net->layers[l];
+                ly->dmin = plan.nets[index].forward[l];
                 digit_weights(ly->W64, ly->n_out, ly->n_in, ly->Wd, ly->wback);
+                if (!(ly->hidden ? net->digits_back : net->digits_out)) continue;
+                ly->dtmin = plan.nets[index].back[l];
                 digit_weights(ly->WT64, ly->n_in, ly->n_pad, ly->WTd, ly->wtback);
             }
         if (net->digits) NS_HIP(hipStreamSynchronize(nullptr));   // calls may come on any stream
@@ -360,8 +309,8 @@ static void build_model(ns_model* m, const ns_model_desc* D) {
     NS_CHECK(D->n_nets == want_nets, NS_E_SHAPE, "wrong number of emulator networks for this model kind");
     const int mu_rows = D->kind == NS_MODEL_SHEAR ? D->n_z : 1;
     NS_CHECK(mu_rows >= 1, NS_E_SHAPE, "n_z must be >= 1");
-    const bool digits = digits_admitted(D);
-    for (int i = 0; i < D->n_nets; ++i) m->nets.push_back(build_net(D->nets[i], mu_rows, digits));
+    const DigitPlan plan = digit_plan(D);
+    for (int i = 0; i < D->n_nets; ++i) m->nets.push_back(build_net(D->nets[i], mu_rows, plan, i));
     const int n_in = m->nets[0]->dims[0];
     for (auto* n : m->nets) NS_CHECK(n->dims[0] == n_in, NS_E_SHAPE, "networks must share their inputs");
     m->n_data = D->n_data;
@@ -875,14 +824,16 @@ ns_status ns_tuning_report(ns_model* model, char* buf, int64_t buf_len) {
 
 const char* ns_last_error(void) { return g_last_error.c_str(); }
 
-// Not in the ABI's header: the host's decision alone, for tests without a GPU.
-int32_t nsmi_digits_admitted(const ns_model_desc* desc) {
-    int32_t yes = 0;
+// Not in the ABI's header: the host's decision alone, for tests without a GPU
+// (bits: forward, adjoint's hidden layers, adjoint's output layer).
+int32_t nsmi_digit_plan(const ns_model_desc* desc) {
+    int32_t bits = 0;
     (void)guard([&] {
         check_ptr(desc, "desc");
-        yes = digits_admitted(desc) ? 1 : 0;
+        const DigitPlan p = digit_plan(desc);
+        bits = p.forward ? 1 + 2 * p.back + 4 * p.out : 0;
     });
-    return yes;
+    return bits;
 }
 
 }  // extern "C"

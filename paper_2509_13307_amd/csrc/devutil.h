@@ -156,6 +156,15 @@ __device__ __forceinline__ double wave_scan(double v) {
     v += dpp_get<0x143, 0xc>(v);
     return v;
 }
+__device__ __forceinline__ int wave_total(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return __builtin_amdgcn_readlane(v, 63);
+}
 // sum over the wave, the same in every lane
 __device__ __forceinline__ double wave_total(double v) {
     v = wave_scan(v);

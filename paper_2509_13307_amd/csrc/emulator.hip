@@ -567,33 +567,30 @@ __global__ __launch_bounds__(64) void digit_weights_kernel(const double* __restr
                                                            char* __restrict__ tiles, double* __restrict__ back) {
     const int n = blockIdx.x, blk = blockIdx.y, lane = threadIdx.x;
     const int k = blk * DG_K + lane * 8;
-    double x[8];
-    int h = 0;
+    double x[8], mx = 0.0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         x[e] = n < N && k < K ? W[(int64_t)n * K + k + e] : 0.0;
-        h = max(h, __double2hiint(x[e]) & 0x7fffffff);
+        mx = fmax(mx, fabs(x[e]));
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) h = max(h, __shfl_xor(h, o, 64));
-    const DigitScale sc = digit_scale(h);
-    if (lane == 0) back[(int64_t)blk * gridDim.x + n] = sc.back;
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+    const double step = mx > 0.0 ? weight_step(mx) : 0.0, per = mx > 0.0 ? 1.0 / step : 0.0;
+    if (lane == 0) back[(int64_t)blk * gridDim.x + n] = step * 0x1p24;
     if (k >= K) return;
+    uint2 d[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const double v = x[e] * per;                     // and what it misses of x / step
+        d[e] = digits_of_sum(v, fma(-v, step, x[e]) * per);
+    }
     uint32_t a[DG_N], c[DG_N];
-    const double x0[4] = {x[0], x[1], x[2], x[3]}, x1[4] = {x[4], x[5], x[6], x[7]};
-    pack4(x0, sc.to_int, a);
-    pack4(x1, sc.to_int, c);
+    const uint2 d0[4] = {d[0], d[1], d[2], d[3]}, d1[4] = {d[4], d[5], d[6], d[7]};
+    pack4(d0, a);
+    pack4(d1, c);
     char* t = tiles + digit_offset(n, k, K);
 #pragma unroll
     for (int i = 0; i < DG_N; ++i) *reinterpret_cast<uint2*>(t + i * 1024) = make_uint2(a[i], c[i]);
-}
-
-bool digit_shape(const std::vector<int>& dims) {
-    const int L = (int)dims.size() - 1;
-    if (L < 2) return false;
-    for (int l = 1; l < L; ++l)
-        if (dims[l] < 256) return false;
-    return true;
 }
 
 void digit_weights(const DevBuf& W64, int N, int K, DevBuf& tiles, DevBuf& back) {
@@ -605,30 +602,42 @@ void digit_weights(const DevBuf& W64, int N, int K, DevBuf& tiles, DevBuf& back)
     NS_HIP(hipGetLastError());
 }
 
-// One layer of G networks on digits: the rows' fragments (into the model's
-// workspace), then the products.
+// One layer ly[g] of G networks on digits, or its adjoint (`back`): the rows'
+// fragments (into the model's workspace), then the products.
 template <class Epi>
-static void launch_gemm_i8(ns_model* m, const Group<Epi>& P, int64_t rows, int N, int K, int G, const int* count,
-                           int rpw, hipStream_t s) {
+static void launch_gemm_i8(ns_model* m, const Group<Epi>& P, const Layer* const (&ly)[MAXG], bool back, int64_t rows,
+                           int N, int K, int G, const int* count, int rpw, hipStream_t s) {
     const int64_t nb = (N + 31) / 32, rb = (rows + DG_ROWS - 1) / DG_ROWS, m32 = rb * DG_ROWS;
     const int blocks = (K + DG_K - 1) / DG_K;
-    const size_t tile_bytes = (size_t)m32 * K * DG_N, back_bytes = (size_t)m32 * blocks * sizeof(double);
-    m->ws_digits.ensure(G * (tile_bytes + back_bytes));
+    const size_t tile_bytes = (size_t)m32 * K * DG_N, factors = (size_t)m32 * blocks;
+    m->ws_digits.ensure(G * (tile_bytes + factors * sizeof(double)));
+    double* back0 = reinterpret_cast<double*>(m->ws_digits.as<char>() + G * tile_bytes);
     DigitRows R{};
     DigitGroup<Epi> D{};
+    D.lda = K;
+    D.ldw = back ? ly[0]->n_in : ly[0]->n_pad;
+    D.present = back ? ly[0]->n_out : ly[0]->n_in;
     for (int g = 0; g < G; ++g) {
-        NS_CHECK(P.W[g] && P.Wl[g], NS_E_UNSUPPORTED, "network without digit tiles");
+        D.W[g] = back ? ly[g]->WTd.p : ly[g]->Wd.p;
+        D.Wl[g] = back ? ly[g]->wtback.as<double>() : ly[g]->wback.as<double>();
+        NS_CHECK(D.W[g] && D.Wl[g], NS_E_UNSUPPORTED, "layer without digit tiles");
         R.A[g] = static_cast<const double*>(P.A[g]);
         R.tiles[g] = m->ws_digits.as<char>() + g * tile_bytes;
-        R.back[g] = reinterpret_cast<double*>(m->ws_digits.as<char>() + G * tile_bytes + g * back_bytes);
+        R.back[g] = back0 + g * factors;
+        R.minimum[g] = back ? ly[g]->dtmin : ly[g]->dmin;
         D.A[g] = R.tiles[g];
         D.Al[g] = R.back[g];
-        D.W[g] = P.W[g];
-        D.Wl[g] = static_cast<const double*>(P.Wl[g]);
+        D.A64[g] = R.A[g];
+        D.Wk[g] = back ? ly[g]->W64.as<double>() : ly[g]->WT64.as<double>();
         D.epi[g] = P.epi[g];
     }
-    hipLaunchKernelGGL(digit_rows_kernel<0>, dim3((unsigned)((rows + 3) / 4), (unsigned)blocks, (unsigned)G), dim3(256),
-                       0, s, R, (int64_t)K, rows, K, m32, count, rpw);
+    if (blocks == 1)
+        hipLaunchKernelGGL(digit_rows_kernel<false>, dim3((unsigned)((rows + 3) / 4), (unsigned)G), dim3(256), 0, s, R,
+                           (int64_t)K, rows, K, m32, count, rpw);
+    else
+        hipLaunchKernelGGL(digit_rows_kernel<true>, dim3((unsigned)rows, (unsigned)G),
+                           dim3(64 * std::min(blocks, DR_WAVES)), blocks * (sizeof(double) + sizeof(int)), s, R, (int64_t)K,
+                           rows, K, m32, count, rpw);
     const bool multi = K > DG_K;
     const int64_t cus = device_cus(m->device), groups = rb * G;
     auto rounds = [&](int64_t per_row_block) { return (groups * per_row_block + cus - 1) / cus; };
@@ -905,27 +914,31 @@ void emulator_forward(ns_model* m, const int* nets, int G, const double* theta, 
         if (prec == NS_FP64) {
             if (!last) {
                 Group<EpiHidden<double, double>> P{};
+                const Layer* layer[MAXG] = {};
                 for (int g = 0; g < G; ++g) {
                     const Layer& ly = *m->nets[nets[g]]->layers[l];
-                    P.A[g] = A_of(g); P.W[g] = net0.digits ? ly.Wd.p : ly.W64.p; P.Wl[g] = ly.wback.p;
+                    layer[g] = &ly;
+                    P.A[g] = A_of(g); P.W[g] = ly.W64.p;
                     P.epi[g] = {ly.b64.as<double>(), ly.beta64.as<double>(), ly.gamma64.as<double>(),
                                 (double*)D_of(g), (int64_t)N, (double*)tslot(g, l)};
                 }
                 if (net0.digits)
-                    launch_gemm_i8(m, P, rows, N, K, G, count, rpw, s);
+                    launch_gemm_i8(m, P, layer, false, rows, N, K, G, count, rpw, s);
                 else
                     launch_gemm_f64(m, P, (int64_t)K, rows, N, K, G, count, rpw, s);
             } else {
                 Group<EpiOut<double>> P{};
+                const Layer* layer[MAXG] = {};
                 for (int g = 0; g < G; ++g) {
                     const Net& net = *m->nets[nets[g]];
                     const Layer& ly = *net.layers[l];
-                    P.A[g] = A_of(g); P.W[g] = net0.digits ? ly.Wd.p : ly.W64.p; P.Wl[g] = ly.wback.p;
+                    layer[g] = &ly;
+                    P.A[g] = A_of(g); P.W[g] = ly.W64.p;
                     P.epi[g] = {ly.b64.as<double>(), net.out_mu64.as<double>(), net.out_sigma64.as<double>(),
                                 (double*)D_of(g), ldo, net.out_mu_rows, N, is_log[g]};
                 }
                 if (net0.digits)
-                    launch_gemm_i8(m, P, rows, N, K, G, count, rpw, s);
+                    launch_gemm_i8(m, P, layer, false, rows, N, K, G, count, rpw, s);
                 else
                     launch_gemm_f64(m, P, (int64_t)K, rows, N, K, G, count, rpw, s);
             }
@@ -1067,30 +1080,35 @@ static void backward_impl(ns_model* m, const int* nets, int G, int64_t B, const 
         return (const T*)(tbase + ((size_t)g * save_stride + (size_t)slot * act_stride) * sizeof(T));
     };
     int cur = 0;
-    bool done = false;
-    if constexpr (sizeof(T) == 8) {
-        done = emulator_backward_digits(m, nets, G, B, m->ws_gact[0].as<double>(), m->ws_gact[1].as<double>(), gstride,
-                                        (const double*)tbase, save_stride, act_stride, s);
-        if (done) cur = 1;
-    }
-    for (int l = L - 1; l >= 1 && !done; --l) {
+    for (int l = L - 1; l >= 1; --l) {
+        // the remaining layers in one kernel, from the output deltas or, where
+        // the output layer is on FP64 products, from the last hidden layer's
+        if constexpr (sizeof(T) == 8)
+            if (l == (net0.digits_out ? L - 1 : L - 2) &&
+                emulator_backward_digits(m, nets, G, B, m->ws_gact[0].as<double>(), m->ws_gact[1].as<double>(),
+                                         gstride, (const double*)tbase, save_stride, act_stride, s)) {
+                cur = 1;
+                break;
+            }
         const int Kred = net0.layers[l]->n_pad, Nout = net0.dims[l];
         TraceScope ts(m, s, f64 ? "adj_gemm_f64" : "adj_gemm_f32");
+        const bool digits = f64 && (l == L - 1 ? net0.digits_out : net0.digits_back);
+        const Layer* layer[MAXG] = {};
         Group<EpiBack<T>> P{};
         for (int g = 0; g < G; ++g) {
             const Net& net = *m->nets[nets[g]];
             const Layer& ly = *net.layers[l];
             const Layer& lb = *net.layers[l - 1];
             P.A[g] = m->ws_gact[cur].as<T>() + g * gstride;
-            P.W[g] = f64 ? (net0.digits ? ly.WTd.p : ly.WT64.p) : ly.WT32.p;
-            P.Wl[g] = ly.wtback.p;
+            P.W[g] = f64 ? ly.WT64.p : ly.WT32.p;
+            layer[g] = &ly;
             P.epi[g] = {tslot(g, l - 1), (const T*)(f64 ? lb.beta64.p : lb.beta32.p),
                         (const T*)(f64 ? lb.gamma64.p : lb.gamma32.p), m->ws_gact[cur ^ 1].as<T>() + g * gstride,
                         (int64_t)Nout};
         }
         if constexpr (sizeof(T) == 8) {
-            if (net0.digits)
-                launch_gemm_i8(m, P, rows, Nout, Kred, G, count, rpw, s);
+            if (digits)
+                launch_gemm_i8(m, P, layer, true, rows, Nout, Kred, G, count, rpw, s);
             else
                 launch_gemm_f64(m, P, (int64_t)Kred, rows, Nout, Kred, G, count, rpw, s);
         } else

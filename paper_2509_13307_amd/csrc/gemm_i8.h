@@ -1,19 +1,31 @@
 // FP64 products on the int8 matrix cores (gfx950), for the wide emulator
-// layers in the NS_FP64 form.
+// layers in the NS_FP64 form: Ozaki-type splitting (Ozaki et al. 2012, on
+// integer matrix units Ootomo et al. 2024) with one scale per row and block.
 //
-// Each operand row is scaled by a power of two over blocks of DG_K = 512
-// inputs and rounded to a 55-bit integer v, |v| < 127 2^48, written as seven
-// balanced base-256 digits (v = sum_i d_i 256^(6-i), d_i a signed byte).  The
-// digit products d_i e_j with i + j <= 6 (28 of the 49) are summed by
-// v_mfma_i32_32x32x32_i8 in one int32 accumulator per i + j, exactly: at most
-// 7 x 512 products of 2^14 stay below 2^26.  The accumulators form
+// Over blocks of DG_K = 512 inputs, a row's entries are rounded to multiples of
+// 2^(e-54), 2^e <= the largest entry, and a unit's weights to multiples of a
+// step of eight significant bits just above their largest / (127 2^48): 55-bit
+// integers v, |v| <= 127 2^48, written as seven balanced base-256 digits
+// (v = sum_i d_i 256^(6-i), d_i a signed byte).  The digit products d_i e_j
+// with i + j <= 6 (28 of the 49) are summed by v_mfma_i32_32x32x32_i8 in one
+// int32 accumulator per i + j, exactly: at most 7 x 512 products of 2^14 stay
+// below 2^26.  The accumulators form
 //   T = 2^24 (a0 2^24 + a1 2^16 + a2 2^8 + a3) + (a4 2^16 + a5 2^8 + a6)
-// with one rounding, and the result is T times the two scales.  The dropped
-// digit products are below 2^-54 of the operands' largest entries, less than
-// the roundings of 512 FP64 multiply-adds: over the emulators' layers the
-// error against extended precision is half that of the FP64 product.  Integer
-// sums have no order, so a row's result does not depend on the batch, the
-// tile or the launch shape.
+// with one rounding, and the result is T times the two steps.  Integer sums
+// have no order, so a row's result does not depend on the batch, the tile or
+// the launch shape.
+//
+// Error of one product, relative to the product of the blocks' largest
+// entries: the six dropped pairs of i + j = 7 are at most 6 2^14 2^40 of at
+// least 2^108.9, 2^-52.3 (rms over random digits about 2^-56); the operands'
+// rounding is below 2^-54 of each block's largest entry.  An FP64 product is
+// relative to its own size instead, so digits are the better of the two only
+// where a row's entries, and a unit's weights, are of similar size.  Both are
+// checked: the weights on the host (digit_rule.cpp), and every row where it is
+// converted, from the sum of squares of its leading digits; a row that fails,
+// or holds infinities, NaN or values beyond 2^(+-900), takes FP64 products in
+// the same kernels (fp64_rows below).  On rows that pass, the error against
+// extended precision is below an FP64 chain's (a third of it for normal draws).
 //
 // Why: v_mfma_f64_16x16x4f64 peaks at 73 TFLOP/s on this chip; the int8 pipe
 // sustains 3400 TOPS on random digits (power bound), 121 TFLOP/s of 28-fold
@@ -41,23 +53,60 @@ constexpr int DG_PLANE = DG_ROWS * DG_LDS;      // bytes per digit plane
 // values they start from in scratch memory meanwhile.
 __device__ __forceinline__ void pin(double& v) { asm volatile("" : "+v"(v)); }
 
+constexpr double DG_FP64 = -1.0;                // factor of a row that takes FP64 products in any case
+
 // Scale of a row from the high word of its largest magnitude: exponent e with
 // max < 127/128 2^(e+1).  to_int: multiplier to the integer v; back: the
-// factor of T (half of the 2^48 that T's integer weights leave out).
+// factor of T (half of the 2^48 that T's integer weights leave out), 0 for a
+// row of zeros; both 0 for a row outside 2^(+-900), infinities and NaN too.
 struct DigitScale {
     double to_int, back;
 };
 __device__ __forceinline__ DigitScale digit_scale(int max_hi) {
     const int ef = (max_hi + 0x4000) >> 20;                       // biased exponent
-    const int e = max(ef, 64) - 1023;                             // below 2^-959: digits keep fewer bits
+    const bool in = ef > 1023 - 900 && ef < 1023 + 900;
     DigitScale s;
-    s.to_int = __longlong_as_double((long long)(54 - e + 1023) << 52);
-    s.back = max_hi == 0 ? 0.0 : __longlong_as_double((long long)(e - 30 + 1023) << 52);
-    if (ef >= 0x7ff) {                                            // infinity or NaN in the row
-        s.to_int = 0.0;
-        s.back = __longlong_as_double(0x7ff8000000000000ll);
-    }
+    s.to_int = in ? __longlong_as_double((long long)(54 + 1023 + 1023 - ef) << 52) : 0.0;
+    s.back = in ? __longlong_as_double((long long)(ef - 30) << 52) : 0.0;
     return s;
+}
+// Whether digits serve a row of one block: its largest magnitude's high word,
+// and the sum of squares of its leading digits against the layer's minimum.
+__device__ __forceinline__ bool digit_row(int max_hi, int squares, int minimum) {
+    return squares >= minimum || max_hi == 0;
+}
+// A row's factor, marked where no digits can hold it.
+__device__ __forceinline__ double row_factor(int max_hi) {
+    const double back = digit_scale(max_hi).back;
+    return back == 0.0 && max_hi != 0 ? DG_FP64 : back;
+}
+// The same over several blocks of K inputs: each block's squares, and its share
+// of the inputs, weigh with its factor's square.
+__device__ __forceinline__ bool digit_row(const double* factors, const int* squares, int stride, int K, int minimum) {
+    const int blocks = (K + DG_K - 1) / DG_K;
+    double most = 0.0;
+    bool held = true;
+    for (int b = 0; b < blocks; ++b) {
+        const double f = factors[b * stride];
+        held &= f >= 0.0;
+        most = fmax(most, f);
+    }
+    double have = 0.0, need = 0.0;
+    for (int b = 0; b < blocks && most > 0.0; ++b) {
+        const double q = factors[b * stride] / most, q2 = q * q;
+        have += squares[b * stride] * q2;
+        need += min(DG_K, K - b * DG_K) * q2;
+    }
+    return held && have * K >= minimum * need;
+}
+// The rows of a row block that digits do not serve (lane % 32, those that are
+// `in`), a bit each: marked by their factors.
+__device__ __forceinline__ uint32_t fp64_set(const double* factors, bool in, int lane) {
+    return (uint32_t)__ballot(in && factors[lane & 31] < 0.0);
+}
+// Sum of squares of the four leading digits in a word, added to s.
+__device__ __forceinline__ int digit_squares(uint32_t d0, int s) {
+    return __builtin_amdgcn_sdot4((int)d0, (int)d0, s, false);
 }
 
 // Seven balanced digits of x * to_int, least significant in byte 0.  The
@@ -72,6 +121,22 @@ __device__ __forceinline__ uint2 digits_of(double x, double to_int) {
     const int h = __double2loint(y);
     const unsigned long long q = ((unsigned long long)(long long)h << 24) + (uint32_t)__double2loint(z);
     return make_uint2((uint32_t)q ^ 0x80808080u, (uint32_t)(q >> 32) ^ 0x00008080u);
+}
+
+// The same of v + dv, |dv| <= 2^4.
+__device__ __forceinline__ uint2 digits_of_sum(double v, double dv) {
+    constexpr double MAGIC = 0x1.8p52 + 0x808080;
+    const double y = fma(v, 0x1p-24, MAGIC);
+    const double z = (fma(y - MAGIC, -0x1p24, v) + dv) + MAGIC;
+    const int h = __double2loint(y);
+    const unsigned long long q = ((unsigned long long)(long long)h << 24) + (uint32_t)__double2loint(z);
+    return make_uint2((uint32_t)q ^ 0x80808080u, (uint32_t)(q >> 32) ^ 0x00008080u);
+}
+
+// Step of a unit's weights of which mx > 0 is the largest: eight significant
+// bits, so that w / step rounds exactly, and no more than 1/128 wide of the mark.
+__device__ __forceinline__ double weight_step(double mx) {
+    return __hiloint2double((__double2hiint(mx * (0x1p-48 / 127.0)) + 0x1000) & ~0xfff, 0);
 }
 
 // Bytes 0..3 of four words -> word b holds byte b of each (a 4 x 4 transpose).
@@ -95,18 +160,23 @@ __device__ __forceinline__ int64_t digit_offset(int64_t r, int k, int K) {
 
 // Digit words of four consecutive inputs of a row: o[i] holds digit i (0 most
 // significant) of the four.
-__device__ __forceinline__ void pack4(const double (&x)[4], double to_int, uint32_t (&o)[DG_N]) {
+__device__ __forceinline__ void pack4(const uint2 (&d)[4], uint32_t (&o)[DG_N]) {
     uint32_t lo[4], hi[4], tl[4], th[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const uint2 d = digits_of(x[k], to_int);
-        lo[k] = d.x;
-        hi[k] = d.y;
+        lo[k] = d[k].x;
+        hi[k] = d[k].y;
     }
     byte_transpose(lo, tl);
     byte_transpose(hi, th);
     o[0] = th[2]; o[1] = th[1]; o[2] = th[0];
     o[3] = tl[3]; o[4] = tl[2]; o[5] = tl[1]; o[6] = tl[0];
+}
+
+__device__ __forceinline__ void pack4(const double (&x)[4], double to_int, uint32_t (&o)[DG_N]) {
+    const uint2 d[4] = {digits_of(x[0], to_int), digits_of(x[1], to_int), digits_of(x[2], to_int),
+                        digits_of(x[3], to_int)};
+    pack4(d, o);
 }
 
 // One K step of 32: the 28 digit products of the row fragments x and the unit
@@ -149,6 +219,13 @@ __device__ __forceinline__ double digit_value(const i32x16_t (&acc)[DG_N], int r
     return fma(h, 0x1p24, l);
 }
 
+// T times the row's and the unit's factors.  The second product rounds: it is
+// not to be fused with what a kernel adds to it, so that all kernels agree.
+__device__ __forceinline__ double digit_product(double T, double row, double unit) {
+#pragma clang fp contract(off)
+    return (T * row) * unit;
+}
+
 // The 32 x kc values (kc <= DG_K) of rows [m0, m0 + 32) of A (FP64, row stride
 // lda) from input k0 on, to digit planes in LDS by a workgroup of eight waves,
 // and each row's factor; rows past M are zero.  Wave w takes rows 4 w .. + 3, a
@@ -170,8 +247,8 @@ struct PlaneRows {
                 x[q][s][0] = a.x; x[q][s][1] = a.y; x[q][s][2] = b.x; x[q][s][3] = b.y;
             }
     }
-    __device__ __forceinline__ void store(char* planes, double* back, int kc, int wave, int lane) const {
-        int mx[4];
+    __device__ __forceinline__ void store(char* planes, double* back, int* squares, int kc, int wave, int lane) const {
+        int mx[4], sq[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             mx[q] = 0;
@@ -185,15 +262,24 @@ struct PlaneRows {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const DigitScale sc = digit_scale(mx[q]);
-            if (lane == 0) back[4 * wave + q] = sc.back;
+            sq[q] = 0;
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
                 if (256 * s + 4 * lane >= kc) continue;
                 uint32_t d[DG_N];
                 pack4(x[q][s], sc.to_int, d);
+                sq[q] = digit_squares(d[0], sq[q]);
                 char* dst = planes + (4 * wave + q) * DG_LDS + 256 * s + 4 * lane;
 #pragma unroll
                 for (int i = 0; i < DG_N; ++i) *reinterpret_cast<uint32_t*>(dst + i * DG_PLANE) = d[i];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int sum = wave_total(sq[q]);
+            if (lane == 0) {
+                back[4 * wave + q] = row_factor(mx[q]);
+                squares[4 * wave + q] = sum;
             }
         }
     }
@@ -201,48 +287,111 @@ struct PlaneRows {
 
 // Digit fragments of A [M x K] (FP64, row stride lda): tiles
 // [M / 32][K / 32][7][lane][16 bytes], and the rows' factors [block of DG_K
-// inputs][M rounded up to 32].  One wave per (row, block).  A launch of its
-// own: every tile of a layer reads the same fragments, and converting a row
+// inputs][M rounded up to 32], all DG_FP64 for a row that digits do not serve.
+// One wave per (row, block).  A launch of its own: every tile of a layer reads the same fragments, and converting a row
 // block's 16 384 values in each of a layer's 16 or more workgroups took 3 us
 // of each one's 7.
 struct DigitRows {
     const double* A[4];
     char* tiles[4];
     double* back[4];
+    int minimum[4];                                      // digit_row
 };
-template <int>
-__global__ __launch_bounds__(256) void digit_rows_kernel(DigitRows P, int64_t lda, int64_t M, int K, int64_t m32,
+constexpr int DR_WAVES = 8;
+// MULTI: a workgroup has one row, a wave every DR_WAVES'th block of it.
+template <bool MULTI>
+__global__ __launch_bounds__(MULTI ? 64 * DR_WAVES : 256) void digit_rows_kernel(DigitRows P, int64_t lda, int64_t M, int K, int64_t m32,
                                                          const int* __restrict__ count, int rows_per_count) {
-    const int g = blockIdx.z, blk = blockIdx.y, lane = threadIdx.x & 63;
+    const int g = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (count) M = min<int64_t>(M, (int64_t)(*count) * rows_per_count);
-    const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t r = MULTI ? blockIdx.x : (int64_t)blockIdx.x * 4 + wave;
     if (r >= M) return;
-    const int k = blk * DG_K + lane * 4;                 // and + 256
-    const double* src = P.A[g] + r * lda + k;
-    double x[2][4];
-    int h = 0;
+    extern __shared__ __attribute__((aligned(16))) char dr_lds[];
+    const int blocks = MULTI ? (K + DG_K - 1) / DG_K : 1;
+    double* factors = reinterpret_cast<double*>(dr_lds);
+    int* squares = reinterpret_cast<int*>(factors + blocks);
+    for (int blk = MULTI ? wave : 0; blk < blocks; blk += DR_WAVES) {
+        const int k = blk * DG_K + lane * 4;             // and + 256
+        const double* src = P.A[g] + r * lda + k;
+        double x[2][4];
+        int h = 0;
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const bool in = k + 256 * s < min(K, (blk + 1) * DG_K);
-        const double2* q = reinterpret_cast<const double2*>(in ? src + 256 * s : P.A[g]);
-        const double2 a = in ? q[0] : make_double2(0.0, 0.0), b = in ? q[1] : make_double2(0.0, 0.0);
-        x[s][0] = a.x; x[s][1] = a.y; x[s][2] = b.x; x[s][3] = b.y;
+        for (int s = 0; s < 2; ++s) {
+            const bool in = k + 256 * s < min(K, (blk + 1) * DG_K);
+            const double2* q = reinterpret_cast<const double2*>(in ? src + 256 * s : P.A[g]);
+            const double2 a = in ? q[0] : make_double2(0.0, 0.0), b = in ? q[1] : make_double2(0.0, 0.0);
+            x[s][0] = a.x; x[s][1] = a.y; x[s][2] = b.x; x[s][3] = b.y;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) h = max(h, __double2hiint(x[s][e]) & 0x7fffffff);
+            for (int e = 0; e < 4; ++e) h = max(h, __double2hiint(x[s][e]) & 0x7fffffff);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) h = max(h, __shfl_xor(h, o, 64));
+        const DigitScale sc = digit_scale(h);
+        int sq = 0;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int ks = k + 256 * s;
+            if (ks >= K) break;
+            uint32_t d[DG_N];
+            pack4(x[s], sc.to_int, d);
+            sq = digit_squares(d[0], sq);
+            char* t = P.tiles[g] + digit_offset(r, ks, K);
+#pragma unroll
+            for (int i = 0; i < DG_N; ++i) *reinterpret_cast<uint32_t*>(t + i * 1024) = d[i];
+        }
+        sq = wave_total(sq);
+        if (lane > 0) continue;
+        if (MULTI) {
+            factors[blk] = row_factor(h);
+            squares[blk] = sq;
+        } else {
+            P.back[g][r] = digit_row(h, sq, P.minimum[g]) ? row_factor(h) : DG_FP64;
+        }
+    }
+    if (!MULTI) return;
+    __syncthreads();
+    const bool served = digit_row(factors, squares, 1, K, P.minimum[g]);
+    for (int b = threadIdx.x; b < blocks; b += 64 * DR_WAVES) P.back[g][b * m32 + r] = served ? factors[b] : DG_FP64;
+}
+
+// The rows of a tile that take FP64 products.  The sum over a block of inputs
+// is the same in every kernel: fused multiply-adds in order over its first 256
+// inputs and over the rest, then the two added.
+//
+// One wave, up to four rows (x[j], inputs k of the block), 32 units of which
+// the lane has one (w: its weights, `ldw` apart per input): lanes 0 .. 31 take
+// the first 256 inputs, the others the rest; all get the sums.  Inputs from
+// `present` on have no weights (they are zeros), the block has kc of them (a
+// multiple of 32).
+__device__ __forceinline__ void fp64_rows(const double* const (&x)[4], const double* __restrict__ w, int64_t ldw, int kc,
+                                          int present, int lane, double (&y)[4]) {
+    const int k0 = (lane >> 5) * 256, k1 = min(kc, k0 + 256);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) y[j] = 0.0;
+#pragma unroll 1
+    for (int k = k0; k < k1; k += 8) {
+        double b[8], a[4][8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) b[e] = w[min(k + e, present - 1) * ldw];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a[j][e] = x[j][k + e];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) y[j] = fma(a[j][e], b[e], y[j]);
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) h = max(h, __shfl_xor(h, o, 64));
-    const DigitScale sc = digit_scale(h);
-    if (lane == 0) P.back[g][(int64_t)blk * m32 + r] = sc.back;
+    for (int j = 0; j < 4; ++j) y[j] = y[j] + __shfl_xor(y[j], 32, 64);
+}
+// The next four rows of the set `rem`, taken out of it (the last one again
+// where fewer are left).
+__device__ __forceinline__ void next_rows(uint32_t& rem, int (&r)[4]) {
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const int ks = k + 256 * s;
-        if (ks >= K) break;
-        uint32_t d[DG_N];
-        pack4(x[s], sc.to_int, d);
-        char* t = P.tiles[g] + digit_offset(r, ks, K);
-#pragma unroll
-        for (int i = 0; i < DG_N; ++i) *reinterpret_cast<uint32_t*>(t + i * 1024) = d[i];
+    for (int j = 0; j < 4; ++j) {
+        r[j] = rem ? __builtin_ctz(rem) : r[j > 0 ? j - 1 : 0];
+        rem &= rem - 1;
     }
 }
 
@@ -253,7 +402,11 @@ __global__ __launch_bounds__(256) void digit_rows_kernel(DigitRows P, int64_t ld
 // integer parts of T add up in LDS, exactly, and all 512 threads finish the
 // 1024 outputs.  MULTI: more than DG_K inputs, in blocks whose contributions
 // are added in order (tpw <= GI_TPW).  A, W: digit fragments of the rows and of
-// the units; Al, Wl: their factors [block][m32 or N rounded up to 32].
+// the units; Al, Wl: their factors [block][m32 or N rounded up to 32].  Rows
+// that digits do not serve (fp64_set) are left out and formed at the end, from
+// A64 (row stride lda) and the weights Wk, input by input (stride ldw,
+// `present` inputs): there nothing else holds registers, and a launch without
+// such rows does not fetch the code.
 constexpr int GI_TPW = 4;
 
 template <class Epi> struct DigitGroup {
@@ -261,8 +414,42 @@ template <class Epi> struct DigitGroup {
     const double* Al[4];
     const void* W[4];
     const double* Wl[4];
+    const double* A64[4];
+    const double* Wk[4];
+    int64_t lda, ldw;
+    int present;
     Epi epi[4];
 };
+
+// Rows `odd` of the row block at m0 in tiles [t0, t0 + nt): four rows of a tile
+// per wave at a time, their blocks' sums added in order.
+template <class Epi>
+__device__ __forceinline__ void fp64_tiles(const DigitGroup<Epi>& G, int g, uint32_t odd, int64_t m0, int N, int K,
+                                           int t0, int nt, int wave, int waves, int lane) {
+    const Epi& epi = G.epi[g];
+    const int sets = (__popc(odd) + 3) / 4, per = epi.period();
+    for (int e = wave; e < sets * nt; e += waves) {
+        uint32_t rem = odd;
+        int rr[4] = {};
+        for (int q = 0; q <= e % sets; ++q) next_rows(rem, rr);
+        const int c = (t0 + e / sets) * 32 + (lane & 31), cc = min(c, N - 1);
+        double y[4] = {};
+        for (int k0 = 0; k0 < K; k0 += DG_K) {
+            const double* x[4];
+            double v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[j] = G.A64[g] + (m0 + rr[j]) * G.lda + k0;
+            fp64_rows(x, G.Wk[g] + k0 * G.ldw + cc, G.ldw, min(DG_K, K - k0), G.present - k0, lane, v);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) y[j] = k0 ? y[j] + v[j] : v[j];
+        }
+        if (lane >= 32 || c >= N) continue;
+        const auto col = epi.col(c);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            epi.store(m0 + rr[j], c, col, y[j], epi.pre(m0 + rr[j], c, per ? (int)((m0 + rr[j]) % per) : 0));
+    }
+}
 
 template <class Epi, bool MULTI>
 __global__ __launch_bounds__(512) void gemm_i8_kernel(DigitGroup<Epi> G, int64_t m32, int64_t M, int N, int K, int tpw,
@@ -281,6 +468,7 @@ __global__ __launch_bounds__(512) void gemm_i8_kernel(DigitGroup<Epi> G, int64_t
     const i32x4_t* X = static_cast<const i32x4_t*>(G.A[g]) + ((int64_t)blockIdx.y * KB + wave) * (DG_N * 64) + lane;
     const i32x4_t* W = static_cast<const i32x4_t*>(G.W[g]) + ((int64_t)t0 * KB + wave) * (DG_N * 64) + lane;
     const int ec = tid & 31, er = tid >> 5;              // epilogue: column, rows er and er + 16
+    const uint32_t odd = fp64_set(xback, m0 + (lane & 31) < M, lane);
     double tot[MULTI ? GI_TPW : 1][2];
     int zr[2] = {0, 0};
     if (const int per = epi.period()) {
@@ -361,13 +549,13 @@ __global__ __launch_bounds__(512) void gemm_i8_kernel(DigitGroup<Epi> G, int64_t
                 const double T = digit_value((long long)sums[buf][0][e], (long long)sums[buf][1][e]);
                 sums[buf][0][e] = 0;
                 sums[buf][1][e] = 0;
-                double y = (T * xb[i]) * wb;
+                double y = digit_product(T, xb[i], wb);
                 if (MULTI) {
                     if (k0) y = tot[t][i] + y;
                     tot[t][i] = y;
                 }
                 const int64_t r = m0 + er + 16 * i;
-                if (last && r < M && c < N) epi.store(r, c, col, y, pre[i]);
+                if (last && r < M && c < N && !(odd >> (er + 16 * i) & 1)) epi.store(r, c, col, y, pre[i]);
             }
             buf ^= 1;
         };
@@ -382,6 +570,7 @@ __global__ __launch_bounds__(512) void gemm_i8_kernel(DigitGroup<Epi> G, int64_t
             for (int t = 0; t < nt; ++t) tile(t, std::true_type{});
         }
     }
+    if (__builtin_expect(odd != 0, 0)) fp64_tiles(G, g, odd, m0, N, K, t0, nt, wave, 8, lane);
 }
 
 // The same layer for more tiles: a workgroup of WAVES waves copies its 32
@@ -408,6 +597,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_i8_wide_kernel(DigitGroup<Epi
     const i32x4_t* X = static_cast<const i32x4_t*>(G.A[g]) + (int64_t)blockIdx.y * KB * (DG_N * 64);
     const i32x4_t* W = static_cast<const i32x4_t*>(G.W[g]) + (int64_t)t0 * KB * (DG_N * 64) + lane;
     const double* xback = G.Al[g] + m0 + (lane >> 5) * 4;        // + 8 (r / 4) + r % 4
+    const uint32_t odd = fp64_set(G.Al[g] + m0, m0 + (lane & 31) < M, lane);
     const char* xa = lds + lane * 16;
     int* zrow = reinterpret_cast<int*>(lds + GW_ZR);
     const int per = epi.period();
@@ -460,7 +650,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_i8_wide_kernel(DigitGroup<Epi
             double y[16];
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                y[r] = (digit_value(acc, r) * xback[blk * m32 + (r >> 2) * 8 + (r & 3)]) * wb;
+                y[r] = digit_product(digit_value(acc, r), xback[blk * m32 + (r >> 2) * 8 + (r & 3)], wb);
                 if (MULTI) {
                     if (k0) y[r] = tot[r] + y[r];
                     tot[r] = y[r];
@@ -470,7 +660,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_i8_wide_kernel(DigitGroup<Epi
             }
             if (!last || col >= N) continue;
             const int64_t row0 = m0 + (lane >> 5) * 4;
-            const bool whole = m0 + DG_ROWS <= M;
+            const bool whole = m0 + DG_ROWS <= M && odd == 0;
 #pragma unroll
             for (int h = 0; h < 16; h += 4) {
                 if (whole)
@@ -479,12 +669,14 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_i8_wide_kernel(DigitGroup<Epi
                 else
 #pragma unroll
                     for (int r = h; r < h + 4; ++r)
-                        if (row0 + (r >> 2) * 8 + (r & 3) < M)
+                        if (row0 + (r >> 2) * 8 + (r & 3) < M &&
+                            !(odd >> ((lane >> 5) * 4 + (r >> 2) * 8 + (r & 3)) & 1))
                             epi.store(row0 + (r >> 2) * 8 + (r & 3), col, q, y[r], pre[r]);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
     }
+    if (__builtin_expect(odd != 0, 0)) fp64_tiles(G, g, odd, m0, N, K, t0, nt, wave, WAVES, lane);
 }
 
 }  // namespace nsmi

@@ -23,9 +23,16 @@
 // replaced took 1 380 us (50 TFLOP/s), and the adjoint of 32 768 rows of one
 // 8-512^4-420 network 1 460 us against 990 us now.
 //
+// A layer's rows that digits do not serve (gemm_i8.h) take FP64 products: the
+// workgroup forms their next layer from the values themselves, four rows at a
+// time through LDS, before it goes on with the digits of the others.  4 096
+// rows of a 6-512^4-2500 network with one such layer for every row: 580 us
+// (even rows 347, FP64 products throughout 435); 500 rows, layer by layer, 156
+// (107, 142).
+//
 // Every value is that of the layer-by-layer kernels (exact integer sums, the
-// same scales and epilogue expressions), so a row's result does not depend on
-// which of the two a batch takes.
+// same scales, rows on FP64 products and epilogue expressions), so a row's
+// result does not depend on which of the two a batch takes.
 #include "gemm_i8.h"
 #include "nsmi.h"
 
@@ -37,22 +44,28 @@ constexpr int DM_STEP = DG_N * 64;                  // 16-byte units of one K st
 // offset from one base register (behind the planes each address would take a
 // register of its own)
 constexpr int DM_MAX = 4 * DM_H * 8;                // after the layer parameters [4][512]: row maxima [2][32]
-constexpr int DM_BACK = DM_MAX + 2 * DG_ROWS * 4;   // row factors [32]
+constexpr int DM_SQ = DM_MAX + 2 * DG_ROWS * 4;     // rows' sums of squared leading digits [2][32]
+constexpr int DM_BACK = DM_SQ + 2 * DG_ROWS * 4;    // row factors [32]
 constexpr int DM_ZROW = DM_BACK + DG_ROWS * 8;      // rows' redshift nodes [32]
 constexpr int DM_PLANES = DM_ZROW + DG_ROWS * 4;    // digit planes
-constexpr int DM_LDS_BYTES = DM_PLANES + DG_N * DG_PLANE;
+constexpr int DM_ROWS64 = DM_PLANES + DG_N * DG_PLANE;   // four rows of values [4][512]
+constexpr int DM_MAXBLOCKS = 4 * DM_H * 8 / (DG_ROWS * 12);   // blocks whose factors and squares fit there
+constexpr int DM_LDS_BYTES = DM_ROWS64 + 4 * DM_H * 8;
 
 struct DigitLayer {
     const i32x4_t* W;                   // digit tiles
     const double* back;                 // unit factors
+    const double* Wk;                   // weights input by input (FP64 rows)
     const double *b, *beta, *gamma;
+    int minimum;                        // digit_row of the layer's input rows
     double* t;                          // pre-activations [rows x 512]: written by the forward when wanted, read by the adjoint
 };
 struct DigitNet {
     const double *W1, *b1, *be1, *ga1, *shift, *scale;
     double* t1;
     DigitLayer hid[DM_MAXHID];
-    DigitLayer out;                     // output layer (forward: W, back, b; adjoint: W^T's tiles)
+    DigitLayer out;                     // output layer (forward: W, back, b; adjoint: W^T's tiles, none: its adjoint is done)
+    double* y64;                        // scratch [rows x 512]: products of the rows on FP64
     const double *mu, *sigma;
     double* y;                          // forward: outputs; adjoint: delta of the first layer
     const double* delta;                // adjoint: output deltas [rows x n_pad]
@@ -60,7 +73,7 @@ struct DigitNet {
 };
 struct DigitArgs {
     DigitNet net[4];
-    int n_hidden, n_in, N_out, mu_rows, nrb;
+    int n_hidden, n_in, N_out, n_pad, mu_rows, nrb;
     int64_t ldo;
 };
 
@@ -79,9 +92,12 @@ struct DigitWave {
     i32x4_t w[DG_N], x[DG_N];
     i32x16_t acc[DG_N];
     double back;                        // factor of the lane's row
+    uint32_t odd;                       // rows that take FP64 products in the coming layer
 
     __device__ __forceinline__ double* prm(int i) const { return reinterpret_cast<double*>(lds) + i * DM_H; }
     __device__ __forceinline__ int* rmax(int p) const { return reinterpret_cast<int*>(lds + DM_MAX) + p * DG_ROWS; }
+    __device__ __forceinline__ int* rsq(int p) const { return reinterpret_cast<int*>(lds + DM_SQ) + p * DG_ROWS; }
+    __device__ __forceinline__ double* rows64() const { return reinterpret_cast<double*>(lds + DM_ROWS64); }
     __device__ __forceinline__ double* rback() const { return reinterpret_cast<double*>(lds + DM_BACK); }
     // units 8 q + 256 t (+ 0..3) of the lane's row in such a block: a uniform base, the lane's offset and an immediate
     __device__ __forceinline__ double2* units(double* block, int t, int q) const {
@@ -116,10 +132,80 @@ struct DigitWave {
             if (r & 1) __builtin_amdgcn_sched_barrier(0);
         }
     }
-    // the layer's values h (tiles wave and wave + 8) become the next layer's
-    // digit planes; `stage` runs between the barriers
+    // y[row][u] = or += (`add`), for the rows of `odd` and units u < units (whose
+    // weights stand in even rows), the sums of fp64_rows over a block of inputs
+    // (`present` of them with weights); `put` writes a row's values to its place in LDS, zeros
+    // up to 512
     template <class F>
-    __device__ __forceinline__ void to_planes(const double (&h)[2][16], int p, F stage) {
+    __device__ __forceinline__ void products64(F put, const double* Wk, int64_t ldw, int present, int units, double* y,
+                                               int64_t ldy, bool add) const {
+        constexpr int KS = 8;                            // inputs whose weights are in flight together
+        double* xs = rows64();
+        for (uint32_t rem = odd; rem;) {
+            int r[4] = {};
+            next_rows(rem, r);
+            __syncthreads();                             // the places are free, what `put` reads is there
+#pragma unroll
+            for (int j = 0; j < 4; ++j) put(r[j], xs + j * DM_H);
+            __syncthreads();
+            // a lane has two units (a wave 64) and one half of the inputs
+            const int half = (lane >> 5) * 256;
+#pragma unroll 1
+            for (int u = wave * 64 + (lane & 31) * 2; u < units; u += 512) {
+                double v[4][2] = {};
+#pragma unroll 1
+                for (int k = half; k < half + 256; k += KS) {
+                    double2 w[KS];
+#pragma unroll
+                    for (int e = 0; e < KS; ++e)
+                        w[e] = *reinterpret_cast<const double2*>(Wk + min(k + e, present - 1) * ldw + u);
+#pragma unroll
+                    for (int e = 0; e < KS; e += 2)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const double2 x = *reinterpret_cast<const double2*>(xs + j * DM_H + k + e);
+                            v[j][0] = fma(x.y, w[e + 1].x, fma(x.x, w[e].x, v[j][0]));
+                            v[j][1] = fma(x.y, w[e + 1].y, fma(x.x, w[e].y, v[j][1]));
+                        }
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const double sum = v[j][i] + __shfl_xor(v[j][i], 32, 64);
+                        double* o = y + r[j] * ldy + u + i;
+                        if (lane < 32 && u + i < units && (j == 0 || r[j] != r[j - 1])) *o = add ? *o + sum : sum;
+                    }
+            }
+        }
+        __syncthreads();
+    }
+    // the same from the layer's values h
+    __device__ __forceinline__ void products64(const double (&h)[2][16], const double* Wk, int64_t ldw, int units,
+                                               double* y, int64_t ldy) const {
+        products64([&](int r, double* place) {
+            if (row != r) return;
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) place[(wave + 8 * t) * 32 + u0 + (e >> 2) * 8 + (e & 3)] = h[t][e];
+        }, Wk, ldw, DM_H, units, y, ldy, false);
+    }
+    // v = those sums of tile t for a row of `odd`
+    __device__ __forceinline__ void take64(double* block, int t, double (&v)[16]) const {
+        if (!(odd >> row & 1)) return;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const double2* o = units(block, t, q);
+            const double2 a = o[0], b = o[1];
+            v[4 * q] = a.x; v[4 * q + 1] = a.y; v[4 * q + 2] = b.x; v[4 * q + 3] = b.y;
+        }
+    }
+    // the layer's values h (tiles wave and wave + 8) become the next layer's
+    // digit planes, and `odd` is the set of its rows (of those that count) that
+    // digits do not serve; `stage` runs between the barriers
+    template <class F>
+    __device__ __forceinline__ void to_planes(const double (&h)[2][16], int p, bool counts, int minimum, F stage) {
         int mx = 0;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
@@ -132,8 +218,10 @@ struct DigitWave {
         back = sc.back;
         if (wave == 0 && lane < 32) {
             rmax(p ^ 1)[row] = 0;
+            rsq(p ^ 1)[row] = 0;
             rback()[row] = back;
         }
+        int sq = 0;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -141,13 +229,17 @@ struct DigitWave {
                 const double v[4] = {h[t][4 * q], h[t][4 * q + 1], h[t][4 * q + 2], h[t][4 * q + 3]};
                 uint32_t d[DG_N];
                 pack4(v, sc.to_int, d);
+                sq = digit_squares(d[0], sq);
                 char* dst = lds + DM_PLANES + row * DG_LDS + (wave + 8 * t) * 32 + u0 + 8 * q;
 #pragma unroll
                 for (int i = 0; i < DG_N; ++i) *reinterpret_cast<uint32_t*>(dst + i * DG_PLANE) = d[i];
                 __builtin_amdgcn_sched_barrier(0);
             }
+        sq += __shfl_xor(sq, 32, 64);
+        if (lane < 32) atomicAdd(&rsq(p)[row], sq);
         stage();
         __syncthreads();
+        odd = (uint32_t)__ballot(counts && !digit_row(rmax(p)[row], rsq(p)[row], minimum));
         load_x();
     }
 };
@@ -188,7 +280,7 @@ __global__ __launch_bounds__(512) void mlp_i8_kernel(const double* __restrict__ 
     S.prm(0)[tid] = N.b1[tid];
     S.prm(1)[tid] = N.be1[tid];
     S.prm(2)[tid] = N.ga1[tid];
-    if (tid < 2 * DG_ROWS) S.rmax(0)[tid] = 0;
+    if (tid < 2 * DG_ROWS) S.rmax(0)[tid] = S.rsq(0)[tid] = 0;
     int* zrow = reinterpret_cast<int*>(lds + DM_ZROW);
     if (tid < DG_ROWS) zrow[tid] = A.mu_rows > 1 ? (int)((m0 + tid) % A.mu_rows) * A.N_out : 0;
     double xv[NI];
@@ -259,14 +351,18 @@ __global__ __launch_bounds__(512) void mlp_i8_kernel(const double* __restrict__ 
             const DigitLayer& D = N.hid[l];
             pr[0] = D.b[tid]; pr[1] = D.beta[tid]; pr[2] = D.gamma[tid]; pr[3] = D.back[tid];
         }
-        S.to_planes(h, p, [&]() {
+        const DigitLayer& D = l < A.n_hidden ? N.hid[l] : N.out;
+        S.to_planes(h, p, valid, D.minimum, [&]() {
             if (l < A.n_hidden)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) S.prm(i)[tid] = pr[i];
         });
         p ^= 1;
+        if (__builtin_expect(S.odd != 0, 0)) {                                     // the output layer's go to their place among the outputs
+            if (l < A.n_hidden) S.products64(h, D.Wk, DM_H, DM_H, N.y64 + m0 * DM_H, DM_H);
+            else S.products64(h, D.Wk, A.n_pad, A.N_out, N.y + m0 * A.ldo, A.ldo);
+        }
         if (l == A.n_hidden) break;
-        const DigitLayer& D = N.hid[l];
         const i32x4_t* wt = D.W + (int64_t)wave * nkb * DM_STEP + lane;
         const i32x4_t* wl = (l + 1 < A.n_hidden ? N.hid[l + 1].W : N.out.W) +
                             (l + 1 < A.n_hidden || wave * 32 < A.N_out ? (int64_t)wave * nkb * DM_STEP : 0) + lane;
@@ -278,9 +374,15 @@ __global__ __launch_bounds__(512) void mlp_i8_kernel(const double* __restrict__ 
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int u = (wave + 8 * t) * 32 + S.u0 + (r >> 2) * 8 + (r & 3);
-                h[t][r] = (h[t][r] * S.back) * S.prm(3)[u] + S.prm(0)[u];
+                h[t][r] = digit_product(h[t][r], S.back, S.prm(3)[u]) + S.prm(0)[u];
                 pin(h[t][r]);
                 if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+            if (__builtin_expect(S.odd != 0, 0)) {
+                S.take64(N.y64 + m0 * DM_H, t, h[t]);
+                if (S.odd >> S.row & 1)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) h[t][r] += S.prm(0)[(wave + 8 * t) * 32 + S.u0 + (r >> 2) * 8 + (r & 3)];
             }
             if (SAVE && valid) keep(D.t, t);
             activate(t);
@@ -313,10 +415,15 @@ __global__ __launch_bounds__(512) void mlp_i8_kernel(const double* __restrict__ 
             double y[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const double a = (digit_value(S.acc, 4 * q + r) * S.rback()[8 * q + r + S.u0]) * wb;
+                const double a = digit_product(digit_value(S.acc, 4 * q + r), S.rback()[8 * q + r + S.u0], wb);
                 y[r] = mu[4 * q + r] + sg * (a + b);
                 pin(y[r]);
             }
+            if (__builtin_expect(S.odd != 0, 0))
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (S.odd >> (8 * q + r + S.u0) & 1)
+                        y[r] = mu[4 * q + r] + sg * (*reinterpret_cast<const double*>(y0 + (int64_t)(8 * q + r) * A.ldo * 8 + off) + b);
             if (N.is_log)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) y[r] = exp10_of<double>(y[r]);
@@ -352,7 +459,7 @@ __global__ __launch_bounds__(512) void mlp_i8_back_kernel(int64_t rows, int n_pa
     const int wave = S.wave, lane = S.lane;
     const int64_t grow = m0 + S.row;
     const bool valid = grow < rows;
-    if (tid < 2 * DG_ROWS) S.rmax(0)[tid] = 0;
+    if (tid < 2 * DG_ROWS) S.rmax(0)[tid] = S.rsq(0)[tid] = 0;
 
     double h[2][16];
     // delta_l W_l, times f'(t) of the layer below (rows past the end: t = 0)
@@ -378,22 +485,25 @@ __global__ __launch_bounds__(512) void mlp_i8_back_kernel(int64_t rows, int n_pa
     };
     // the output layer: n_pad inputs in blocks of 512
     const int KB = n_pad / 32;
-    {
+    if (N.out.W) {
         const DigitLayer& B = N.hid[A.n_hidden - 1];
         S.prm(1)[tid] = B.beta[tid];
         S.prm(2)[tid] = B.gamma[tid];
     }
     const i32x4_t* wt = N.out.W + (int64_t)wave * KB * DM_STEP + lane;
-    S.load_w(wt);
-    for (int k0 = 0; k0 < n_pad; k0 += DG_K) {
+    int* squares = reinterpret_cast<int*>(S.rows64() + DM_MAXBLOCKS * DG_ROWS);
+    S.load_w(N.out.W ? wt : N.hid[A.n_hidden - 1].W + (int64_t)wave * 16 * DM_STEP + lane);
+    if (!N.out.W) __syncthreads();                       // the row maxima are cleared
+    for (int k0 = 0; k0 < n_pad && N.out.W; k0 += DG_K) {
         const int kc = min(DG_K, n_pad - k0), nkb = kc / 32;
         PlaneRows R;
         R.load(N.delta, n_pad, m0, rows, k0, kc, wave, lane);
         if (k0) __syncthreads();                         // every wave past its reads of the planes
-        R.store(lds + DM_PLANES, S.rback(), kc, wave, lane);
+        double* factors = S.rows64() + k0 / DG_K * DG_ROWS;
+        R.store(lds + DM_PLANES, factors, squares + k0 / DG_K * DG_ROWS, kc, wave, lane);
         S.prm(3)[tid] = N.out.back[(int64_t)(k0 / DG_K) * DM_H + tid];
         __syncthreads();
-        S.back = S.rback()[S.row];
+        S.back = factors[S.row];
         S.load_x();
         const i32x4_t* wk = wt + (int64_t)(k0 / 32) * DM_STEP;
         const i32x4_t* wn = k0 + DG_K < n_pad ? wk + 16 * DM_STEP
@@ -406,20 +516,30 @@ __global__ __launch_bounds__(512) void mlp_i8_back_kernel(int64_t rows, int n_pa
             // lane's own elements): 64 registers of them would spill the loops
             double v[16];
             S.sums(v);
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                v[r] = digit_product(v[r], S.back, S.prm(3)[(wave + 8 * t) * 32 + S.u0 + (r >> 2) * 8 + (r & 3)]);
             if (!valid) continue;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 double2* o = S.units(N.y + m0 * DM_H, t, q);
                 double2 a = make_double2(0.0, 0.0), b = a;
                 if (k0) { a = o[0]; b = o[1]; }
-                const int u = (wave + 8 * t) * 32 + S.u0 + 8 * q;
-                double e[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) e[r] = (v[4 * q + r] * S.back) * S.prm(3)[u + r];
-                o[0] = make_double2(a.x + e[0], a.y + e[1]);
-                o[1] = make_double2(b.x + e[2], b.y + e[3]);
+                o[0] = make_double2(a.x + v[4 * q], a.y + v[4 * q + 1]);
+                o[1] = make_double2(b.x + v[4 * q + 2], b.y + v[4 * q + 3]);
             }
         }
+    }
+    // rows that digits do not serve, all their blocks
+    if (N.out.W) {
+        const double* factors = S.rows64() + S.row;
+        const bool served = n_pad > DG_K ? digit_row(factors, squares + S.row, DG_ROWS, n_pad, N.out.minimum)
+                                         : factors[0] == 0.0 || (factors[0] > 0.0 && squares[S.row] >= N.out.minimum);
+        S.odd = (uint32_t)__ballot(valid && !served);
+        for (int k0 = 0; k0 < n_pad && __builtin_expect(S.odd != 0, 0); k0 += DG_K)
+            S.products64([&](int r, double* place) {
+                place[tid] = k0 + tid < n_pad ? N.delta[(m0 + r) * n_pad + k0 + tid] : 0.0;
+            }, N.out.Wk + (int64_t)k0 * DM_H, DM_H, A.N_out - k0, DM_H, N.y + m0 * DM_H, DM_H, k0 > 0);
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -433,7 +553,7 @@ __global__ __launch_bounds__(512) void mlp_i8_back_kernel(int64_t rows, int n_pa
             }
             h[t][4 * q] = a.x; h[t][4 * q + 1] = a.y; h[t][4 * q + 2] = b.x; h[t][4 * q + 3] = b.y;
         }
-        through(N.hid[A.n_hidden - 1].t, t);
+        if (N.out.W) through(N.hid[A.n_hidden - 1].t, t);
     }
     // the hidden layers: l's W^T takes delta of hidden GEMM layer l to the layer below (l - 1, or the first layer)
     const int nkb = DM_H / 32;
@@ -442,12 +562,13 @@ __global__ __launch_bounds__(512) void mlp_i8_back_kernel(int64_t rows, int n_pa
         const DigitLayer& D = N.hid[l];
         const double be = l > 0 ? N.hid[l - 1].beta[tid] : N.be1[tid], ga = l > 0 ? N.hid[l - 1].gamma[tid] : N.ga1[tid];
         const double wb = D.back[tid];
-        S.to_planes(h, p, [&]() {
+        S.to_planes(h, p, valid, D.minimum, [&]() {
             S.prm(1)[tid] = be;
             S.prm(2)[tid] = ga;
             S.prm(3)[tid] = wb;
         });
         p ^= 1;
+        if (__builtin_expect(S.odd != 0, 0)) S.products64(h, D.Wk, DM_H, DM_H, N.y64 + m0 * DM_H, DM_H);
         const i32x4_t* wk = D.W + (int64_t)wave * nkb * DM_STEP + lane;
         const i32x4_t* wn = (l > 0 ? N.hid[l - 1].W : D.W) + (int64_t)wave * nkb * DM_STEP + lane;
 #pragma unroll
@@ -457,8 +578,9 @@ __global__ __launch_bounds__(512) void mlp_i8_back_kernel(int64_t rows, int n_pa
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int u = (wave + 8 * t) * 32 + S.u0 + (r >> 2) * 8 + (r & 3);
-                h[t][r] = (h[t][r] * S.back) * S.prm(3)[u];
+                h[t][r] = digit_product(h[t][r], S.back, S.prm(3)[u]);
             }
+            if (__builtin_expect(S.odd != 0, 0)) S.take64(N.y64 + m0 * DM_H, t, h[t]);
             through(l > 0 ? N.hid[l - 1].t : N.t1, t);
         }
     }
@@ -483,9 +605,10 @@ __global__ __launch_bounds__(512) void mlp_i8_back_kernel(int64_t rows, int n_pa
 // outputs forward 188 / 186 at 2 880, 208 / 187 at 3 520, and adjoint
 // 116 / 176 at 1 600, 197 / 176 at 2 240, 213 / 176 at 2 880.
 static bool digit_one_kernel(const ns_model* m, const Net& n0, int G, int64_t rows, bool back) {
-    if (!n0.digits || n0.n_layers < 3 || n0.n_layers - 2 > DM_MAXHID) return false;
+    if (!(back ? n0.digits_back : n0.digits) || n0.n_layers < 3 || n0.n_layers - 2 > DM_MAXHID) return false;
     for (int l = 1; l < n0.n_layers; ++l)
         if (n0.dims[l] != DM_H) return false;
+    if (back && n0.layers[n0.n_layers - 1]->n_pad > DM_MAXBLOCKS * DG_K) return false;
     return (rows + DG_ROWS - 1) / DG_ROWS * G * 32 >= (back ? 10 : 13) * (int64_t)device_cus(m->device);
 }
 
@@ -500,12 +623,15 @@ bool emulator_forward_digits(ns_model* m, const int* nets, int G, const double* 
     A.n_hidden = L - 2;
     A.n_in = n0.dims[0];
     A.N_out = n0.dims[L];
+    A.n_pad = n0.layers[L - 1]->n_pad;
     A.mu_rows = rpw;
     A.nrb = (int)((rows + DG_ROWS - 1) / DG_ROWS);
     A.ldo = ldo;
+    m->ws_act[0].ensure((size_t)G * rows * DM_H * sizeof(double));
     for (int g = 0; g < G; ++g) {
         const Net& net = *m->nets[nets[g]];
         DigitNet& N = A.net[g];
+        N.y64 = m->ws_act[0].as<double>() + (size_t)g * rows * DM_H;
         const Layer& l1 = *net.layers[0];
         N.W1 = l1.W64.as<double>(); N.b1 = l1.b64.as<double>();
         N.be1 = l1.beta64.as<double>(); N.ga1 = l1.gamma64.as<double>();
@@ -518,6 +644,8 @@ bool emulator_forward_digits(ns_model* m, const int* nets, int G, const double* 
             D.W = ly.Wd.as<i32x4_t>();
             D.back = ly.wback.as<double>();
             NS_CHECK(D.W && D.back, NS_E_UNSUPPORTED, "network without digit tiles");
+            D.Wk = ly.WT64.as<double>();
+            D.minimum = ly.dmin;
             D.b = ly.b64.as<double>();
             D.beta = ly.beta64.as<double>();
             D.gamma = ly.gamma64.as<double>();
@@ -551,10 +679,13 @@ bool emulator_backward_digits(ns_model* m, const int* nets, int G, int64_t B, co
     if (!digit_one_kernel(m, n0, G, rows, true)) return false;
     DigitArgs A{};
     A.n_hidden = L - 2;
+    A.N_out = n0.dims[L];
     A.nrb = (int)((rows + DG_ROWS - 1) / DG_ROWS);
+    m->ws_act[0].ensure((size_t)G * rows * DM_H * sizeof(double));
     for (int g = 0; g < G; ++g) {
         const Net& net = *m->nets[nets[g]];
         DigitNet& N = A.net[g];
+        N.y64 = m->ws_act[0].as<double>() + (size_t)g * rows * DM_H;
         const Layer& l1 = *net.layers[0];
         N.be1 = l1.beta64.as<double>(); N.ga1 = l1.gamma64.as<double>();
         double* t = const_cast<double*>(tsave) + g * net_stride;
@@ -564,7 +695,9 @@ bool emulator_backward_digits(ns_model* m, const int* nets, int G, int64_t B, co
             DigitLayer& D = l < L - 1 ? N.hid[l - 1] : N.out;
             D.W = ly.WTd.as<i32x4_t>();
             D.back = ly.wtback.as<double>();
-            NS_CHECK(D.W && D.back, NS_E_UNSUPPORTED, "network without digit tiles");
+            NS_CHECK((D.W && D.back) || (l == L - 1 && !n0.digits_out), NS_E_UNSUPPORTED, "network without digit tiles");
+            D.Wk = ly.W64.as<double>();
+            D.minimum = ly.dtmin;
             D.beta = ly.beta64.as<double>();
             D.gamma = ly.gamma64.as<double>();
             D.t = l < L - 1 ? t + l * slot_stride : nullptr;

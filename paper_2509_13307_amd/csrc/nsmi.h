@@ -86,7 +86,8 @@ struct Layer {
     int n_pad = 0;                           // n_out rounded up to 64
     DevBuf WT64, WT32;                       // W^T [n_in x n_pad], zero padded (adjoint)
     DevBuf Wd, wback, WTd, wtback;           // base-256 digit tiles of W and W^T and their units' factors
-                                             // (networks that pass digit_shape; gemm_i8.h)
+                                             // (where the model's DigitPlan has the layer on digits; gemm_i8.h)
+    int dmin = 0, dtmin = 0;                 // ... and their input rows' least sum of squared leading digits
 };
 
 struct Net {
@@ -111,7 +112,9 @@ struct Net {
     // (kq NT + nt) 64, lane q holding W[16 nt + q % 16][4 kq + q / 16] (0 past N)
     bool narrow64 = false;
     DevBuf Wf64;
-    bool digits = false;                     // FP64 GEMM layers run on int8 digits (all networks of a model alike)
+    // FP64 GEMM layers on int8 digits (all networks of a model alike): the forward's
+    // layers, the adjoint's hidden layers, and its output layer
+    bool digits = false, digits_back = false, digits_out = false;
     ~Net();
 };
 
@@ -355,7 +358,9 @@ __device__ __forceinline__ bool support_test(const SupportLoads& s, const double
 // without launching for other networks and for small batches.  tsave (may be
 // nullptr in the forward): pre-activations of hidden layer l + 1 of network g
 // at g net_stride + l slot_stride, [rows x 512].  The adjoint takes the output
-// deltas [rows x n_pad] of network g at g dstride to the first layer's [rows x 512].
+// deltas [rows x n_pad] of network g at delta + g dstride, or, where the output
+// layer's adjoint is not on digits, the last hidden layer's at delta1 + g
+// dstride, to the first layer's [rows x 512] at delta1 + g dstride.
 bool emulator_forward_digits(ns_model* m, const int* nets, int G, const double* theta, int64_t ld, int64_t B,
                              void* const* outs, int64_t ldo, const int* is_log, double* tsave, size_t net_stride,
                              size_t slot_stride, const int* count, hipStream_t s);
@@ -363,11 +368,26 @@ bool emulator_backward_digits(ns_model* m, const int* nets, int G, int64_t B, co
                               size_t dstride, const double* tsave, size_t net_stride, size_t slot_stride,
                               hipStream_t s);
 
-// Networks whose FP64 GEMM layers run as int8 digit products (gemm_i8.h):
-// every hidden width at least 256 (and even weights, see api.cpp).  Narrower layers stay on the FP64 MFMA: at
+// Networks whose FP64 GEMM layers may run as int8 digit products (gemm_i8.h):
+// every hidden width at least 256.  Narrower layers stay on the FP64 MFMA: at
 // 128 inputs a tile's digit products take a quarter of the time, its 1024
 // conversions and activations the same.
 bool digit_shape(const std::vector<int>& dims);
+// The least sum of squared leading digits of an input row that runs on digits
+// against the units W [units x inputs] (element strides su, si), 0 if the
+// layer does not run on digits (digit_rule.cpp).
+int digit_row_minimum(const double* W, int units, int inputs, int64_t su, int64_t si);
+// Which layers of a model run on digits.  One answer for all its networks,
+// because they are launched as one group, whose kernels read every network's
+// digit tiles.  The adjoint's output layer of shear models stays on FP64
+// products: its rows follow the Limber integrand over the k grid, nine in ten
+// of them too uneven for digits.  (A description that build_net refuses: none.)
+struct DigitPlan {
+    bool forward = false, back = false, out = false;
+    struct Rows { std::vector<int> forward, back; };      // digit_row_minimum of each layer
+    std::vector<Rows> nets;
+};
+DigitPlan digit_plan(const ns_model_desc* D);
 // Digit tiles and factors of the device matrix W64 [N x K] (K a multiple of 32).
 void digit_weights(const DevBuf& W64, int N, int K, DevBuf& tiles, DevBuf& back);
 
