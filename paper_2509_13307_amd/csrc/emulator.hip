@@ -602,11 +602,13 @@ void digit_weights(const DevBuf& W64, int N, int K, DevBuf& tiles, DevBuf& back)
     NS_HIP(hipGetLastError());
 }
 
-// One layer ly[g] of G networks on digits, or its adjoint (`back`): the rows'
-// fragments (into the model's workspace), then the products.
+// Rows [row0, row0 + rows) of `all` of one layer ly[g] of G networks on digits,
+// or its adjoint (`back`): the rows' fragments (into the model's workspace),
+// then the products.
 template <class Epi>
-static void launch_gemm_i8(ns_model* m, const Group<Epi>& P, const Layer* const (&ly)[MAXG], bool back, int64_t rows,
-                           int N, int K, int G, const int* count, int rpw, hipStream_t s) {
+static void launch_gemm_i8_part(ns_model* m, const Group<Epi>& P, const Layer* const (&ly)[MAXG], bool back,
+                                int64_t row0, int64_t rows, int64_t all, int N, int K, int G, const int* count,
+                                int rpw, hipStream_t s) {
     const int64_t nb = (N + 31) / 32, rb = (rows + DG_ROWS - 1) / DG_ROWS, m32 = rb * DG_ROWS;
     const int blocks = (K + DG_K - 1) / DG_K;
     const size_t tile_bytes = (size_t)m32 * K * DG_N, factors = (size_t)m32 * blocks;
@@ -633,11 +635,11 @@ static void launch_gemm_i8(ns_model* m, const Group<Epi>& P, const Layer* const 
     }
     if (blocks == 1)
         hipLaunchKernelGGL(digit_rows_kernel<false>, dim3((unsigned)((rows + 3) / 4), (unsigned)G), dim3(256), 0, s, R,
-                           (int64_t)K, rows, K, m32, count, rpw);
+                           (int64_t)K, row0, all, K, m32, count, rpw);
     else
         hipLaunchKernelGGL(digit_rows_kernel<true>, dim3((unsigned)rows, (unsigned)G),
                            dim3(64 * std::min(blocks, DR_WAVES)), blocks * (sizeof(double) + sizeof(int)), s, R, (int64_t)K,
-                           rows, K, m32, count, rpw);
+                           row0, all, K, m32, count, rpw);
     const bool multi = K > DG_K;
     const int64_t cus = device_cus(m->device), groups = rb * G;
     auto rounds = [&](int64_t per_row_block) { return (groups * per_row_block + cus - 1) / cus; };
@@ -659,11 +661,22 @@ static void launch_gemm_i8(ns_model* m, const Group<Epi>& P, const Layer* const 
         if (bytes && m->lds_attr_set.insert((const void*)kern).second)
             NS_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
         const dim3 grid((unsigned)((nb + tpw - 1) / tpw), (unsigned)rb, (unsigned)G);
-        hipLaunchKernelGGL(kern, grid, dim3(64 * waves), bytes, s, D, m32, rows, N, K, (int)tpw, count, rpw);
+        hipLaunchKernelGGL(kern, grid, dim3(64 * waves), bytes, s, D, m32, row0, all, N, K, (int)tpw, count, rpw);
     };
     if (c8 <= c4 && c8 <= c1) go(multi ? gemm_i8_kernel<Epi, true> : gemm_i8_kernel<Epi, false>, t8, 8, 0);
     else if (c4 <= c1) go(multi ? gemm_i8_wide_kernel<Epi, 4, true> : gemm_i8_wide_kernel<Epi, 4, false>, t4, 4, GW_LDS_BYTES);
     else go(multi ? gemm_i8_wide_kernel<Epi, 8, true> : gemm_i8_wide_kernel<Epi, 8, false>, t1, 8, GW_LDS_BYTES);
+}
+
+// All rows, in parts of at most DG_PART: a part fills the chip many times over
+// (at least 2 048 row blocks of eight tiles), and the fragments take 7 bytes
+// per input of a part's rows instead of the whole batch's.
+constexpr int64_t DG_PART = 65536;
+template <class Epi>
+static void launch_gemm_i8(ns_model* m, const Group<Epi>& P, const Layer* const (&ly)[MAXG], bool back, int64_t rows,
+                           int N, int K, int G, const int* count, int rpw, hipStream_t s) {
+    for (int64_t r = 0; r < rows; r += DG_PART)
+        launch_gemm_i8_part(m, P, ly, back, r, std::min(DG_PART, rows - r), rows, N, K, G, count, rpw, s);
 }
 
 // ------------------------------------------------------ BF16 tile autotuner

@@ -300,19 +300,19 @@ struct DigitRows {
 constexpr int DR_WAVES = 8;
 // MULTI: a workgroup has one row, a wave every DR_WAVES'th block of it.
 template <bool MULTI>
-__global__ __launch_bounds__(MULTI ? 64 * DR_WAVES : 256) void digit_rows_kernel(DigitRows P, int64_t lda, int64_t M, int K, int64_t m32,
+__global__ __launch_bounds__(MULTI ? 64 * DR_WAVES : 256) void digit_rows_kernel(DigitRows P, int64_t lda, int64_t row0, int64_t M, int K, int64_t m32,
                                                          const int* __restrict__ count, int rows_per_count) {
     const int g = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (count) M = min<int64_t>(M, (int64_t)(*count) * rows_per_count);
-    const int64_t r = MULTI ? blockIdx.x : (int64_t)blockIdx.x * 4 + wave;
-    if (r >= M) return;
+    const int64_t r = MULTI ? blockIdx.x : (int64_t)blockIdx.x * 4 + wave;   // of this part, from row0 on
+    if (row0 + r >= M) return;
     extern __shared__ __attribute__((aligned(16))) char dr_lds[];
     const int blocks = MULTI ? (K + DG_K - 1) / DG_K : 1;
     double* factors = reinterpret_cast<double*>(dr_lds);
     int* squares = reinterpret_cast<int*>(factors + blocks);
     for (int blk = MULTI ? wave : 0; blk < blocks; blk += DR_WAVES) {
         const int k = blk * DG_K + lane * 4;             // and + 256
-        const double* src = P.A[g] + r * lda + k;
+        const double* src = P.A[g] + (row0 + r) * lda + k;
         double x[2][4];
         int h = 0;
 #pragma unroll
@@ -403,6 +403,7 @@ __device__ __forceinline__ void next_rows(uint32_t& rem, int (&r)[4]) {
 // 1024 outputs.  MULTI: more than DG_K inputs, in blocks whose contributions
 // are added in order (tpw <= GI_TPW).  A, W: digit fragments of the rows and of
 // the units; Al, Wl: their factors [block][m32 or N rounded up to 32].  Rows
+// The launch takes the rows of a part, from row0 on (A and Al are the part's).  Rows
 // that digits do not serve (fp64_set) are left out and formed at the end, from
 // A64 (row stride lda) and the weights Wk, input by input (stride ldw,
 // `present` inputs): there nothing else holds registers, and a launch without
@@ -452,15 +453,15 @@ __device__ __forceinline__ void fp64_tiles(const DigitGroup<Epi>& G, int g, uint
 }
 
 template <class Epi, bool MULTI>
-__global__ __launch_bounds__(512) void gemm_i8_kernel(DigitGroup<Epi> G, int64_t m32, int64_t M, int N, int K, int tpw,
+__global__ __launch_bounds__(512) void gemm_i8_kernel(DigitGroup<Epi> G, int64_t m32, int64_t row0, int64_t M, int N, int K, int tpw,
                                                       const int* __restrict__ count, int rows_per_count) {
     __shared__ unsigned long long sums[2][2][1024];      // [buffer][hi, lo][32 x 32]
     const int g = blockIdx.z;
     if (count) M = min<int64_t>(M, (int64_t)(*count) * rows_per_count);
-    const int64_t m0 = (int64_t)blockIdx.y * DG_ROWS;
+    const int64_t part = (int64_t)blockIdx.y * DG_ROWS, m0 = row0 + part;
     if (m0 >= M) return;
     const double* wback = G.Wl[g];
-    const double* xback = G.Al[g] + m0;
+    const double* xback = G.Al[g] + part;
     const Epi& epi = G.epi[g];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int KB = K / 32, NB = (N + 31) / 32, n32 = NB * 32;
@@ -581,13 +582,13 @@ constexpr int GW_ZR = (DG_K / 32) * DG_N * 1024;           // LDS: fragments, th
 constexpr int GW_LDS_BYTES = GW_ZR + DG_ROWS * 4;
 
 template <class Epi, int WAVES, bool MULTI>
-__global__ __launch_bounds__(64 * WAVES) void gemm_i8_wide_kernel(DigitGroup<Epi> G, int64_t m32, int64_t M, int N,
+__global__ __launch_bounds__(64 * WAVES) void gemm_i8_wide_kernel(DigitGroup<Epi> G, int64_t m32, int64_t row0, int64_t M, int N,
                                                                   int K, int tpw, const int* __restrict__ count,
                                                                   int rows_per_count) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int g = blockIdx.z;
     if (count) M = min<int64_t>(M, (int64_t)(*count) * rows_per_count);
-    const int64_t m0 = (int64_t)blockIdx.y * DG_ROWS;
+    const int64_t part = (int64_t)blockIdx.y * DG_ROWS, m0 = row0 + part;
     if (m0 >= M) return;
     const double* wback = G.Wl[g];
     const Epi& epi = G.epi[g];
@@ -596,8 +597,8 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_i8_wide_kernel(DigitGroup<Epi
     const int t0 = blockIdx.x * tpw, nt = min(tpw, NB - t0);
     const i32x4_t* X = static_cast<const i32x4_t*>(G.A[g]) + (int64_t)blockIdx.y * KB * (DG_N * 64);
     const i32x4_t* W = static_cast<const i32x4_t*>(G.W[g]) + (int64_t)t0 * KB * (DG_N * 64) + lane;
-    const double* xback = G.Al[g] + m0 + (lane >> 5) * 4;        // + 8 (r / 4) + r % 4
-    const uint32_t odd = fp64_set(G.Al[g] + m0, m0 + (lane & 31) < M, lane);
+    const double* xback = G.Al[g] + part + (lane >> 5) * 4;        // + 8 (r / 4) + r % 4
+    const uint32_t odd = fp64_set(G.Al[g] + part, m0 + (lane & 31) < M, lane);
     const char* xa = lds + lane * 16;
     int* zrow = reinterpret_cast<int*>(lds + GW_ZR);
     const int per = epi.period();
