@@ -919,7 +919,8 @@ void emulator_forward(ns_model* m, const int* nets, int G, const double* theta, 
         static const char* names[4][2] = {{"gemm_f64_hidden", "gemm_f64_out"}, {"gemm_f32_hidden", "gemm_f32_out"},
                                           {"gemm_bf16_hidden", "gemm_bf16_out"},
                                           {"gemm_bf16x3_hidden", "gemm_bf16x3_out"}};
-        TraceScope ts(m, s, names[prec][last ? 1 : 0]);
+        const bool digits = prec == NS_FP64 && net0.digits;
+        TraceScope ts(m, s, !digits ? names[prec][last ? 1 : 0] : last ? "gemm_i8_f64_out" : "gemm_i8_f64_hidden");
         char* A0 = m->ws_act[cur].as<char>();
         char* D0 = m->ws_act[cur ^ 1].as<char>();
         auto A_of = [&](int g) { return (const void*)(A0 + g * act_stride * act_elem); };
@@ -935,7 +936,7 @@ void emulator_forward(ns_model* m, const int* nets, int G, const double* theta, 
                     P.epi[g] = {ly.b64.as<double>(), ly.beta64.as<double>(), ly.gamma64.as<double>(),
                                 (double*)D_of(g), (int64_t)N, (double*)tslot(g, l)};
                 }
-                if (net0.digits)
+                if (digits)
                     launch_gemm_i8(m, P, layer, false, rows, N, K, G, count, rpw, s);
                 else
                     launch_gemm_f64(m, P, (int64_t)K, rows, N, K, G, count, rpw, s);
@@ -950,7 +951,7 @@ void emulator_forward(ns_model* m, const int* nets, int G, const double* theta, 
                     P.epi[g] = {ly.b64.as<double>(), net.out_mu64.as<double>(), net.out_sigma64.as<double>(),
                                 (double*)D_of(g), ldo, net.out_mu_rows, N, is_log[g]};
                 }
-                if (net0.digits)
+                if (digits)
                     launch_gemm_i8(m, P, layer, false, rows, N, K, G, count, rpw, s);
                 else
                     launch_gemm_f64(m, P, (int64_t)K, rows, N, K, G, count, rpw, s);
@@ -1104,8 +1105,8 @@ static void backward_impl(ns_model* m, const int* nets, int G, int64_t B, const 
                 break;
             }
         const int Kred = net0.layers[l]->n_pad, Nout = net0.dims[l];
-        TraceScope ts(m, s, f64 ? "adj_gemm_f64" : "adj_gemm_f32");
         const bool digits = f64 && (l == L - 1 ? net0.digits_out : net0.digits_back);
+        TraceScope ts(m, s, digits ? "adj_gemm_i8_f64" : f64 ? "adj_gemm_f64" : "adj_gemm_f32");
         const Layer* layer[MAXG] = {};
         Group<EpiBack<T>> P{};
         for (int g = 0; g < G; ++g) {
