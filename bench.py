@@ -21,7 +21,7 @@ import time
 import numpy as np
 
 MI355X_PEAK = {"bf16": 2500.0, "bf16x3": 2500.0, "fp32": 157.3, "fp64": 78.6}   # dense TFLOP/s
-INT8_PEAK = 5000.0          # TOP/s, dense
+DIGIT_PEAK = 178.6          # FP64 layers as 28 int8 products of digits each: the int8 peak (5000 dense TOP/s) / 28
 HBM_PEAK_GBS = 8000.0
 
 
@@ -88,10 +88,10 @@ def roofline_of(dom, avg_s, prec, m, B, workload):
     K_hid = net["W"][1].shape[1]
     issued = None
     peak_of = MI355X_PEAK[prec]
+    if "_i8" in dom:
+        peak_of = DIGIT_PEAK
     if dom.startswith("mlp_i8"):
-        # FP64 layers as 28 int8 products of 7 digits each: the FP64 work against the int8 peak / 28
         work, unit, bound = n_nets * mlp_flops(net, rows), "TFLOP/s", "mfma"
-        peak_of = round(INT8_PEAK / 28, 1)
     elif dom.startswith("mlp_fused"):
         work = n_nets * mlp_flops(net, rows)
         gemm = n_nets * sum(2.0 * rows * W.shape[0] * W.shape[1] for W in net["W"][1:])
@@ -357,8 +357,10 @@ def adjoint_leg(Model, W, torch, dev):
     """ns_loglike_grad_batch (logL and d logL / d theta by the hand-written
     adjoint) at batch 4096: gradients per second and the rate of the
     emulator's backward GEMMs (input gradients only: the multiply-adds of its
-    forward GEMM layers once more), against the peak of their arithmetic
-    (FP64 for the FP64 form; the reduced forms run the adjoint in FP32)."""
+    forward GEMM layers once more), against the peak of their arithmetic: FP32
+    for the reduced forms; for the FP64 form that of the int8 digit products
+    where the layers run on them (all of the CMB networks', the hidden ones of
+    shear) and the FP64 matrix peak elsewhere, weighted by their work."""
     B = 4096
     out = {}
     for name, precs in (("cmb4x2500", ("fp64", "bf16x3")), ("shear64", ("fp64",))):
@@ -382,15 +384,20 @@ def adjoint_leg(Model, W, torch, dev):
             g.loglike_grad(th, prec)
             tr = g.trace_report()
             g.trace(False)
-            key = "adj_gemm_f64" if prec == "fp64" else "adj_gemm_f32"
-            if prec == "fp64" and "mlp_i8_f64_adjoint" in tr:   # wide networks: all layers in one kernel
-                key = "mlp_i8_f64_adjoint"
-            n_adj, t_adj = tr.get(key, (0, 0.0))
-            peak = MI355X_PEAK["fp64" if prec == "fp64" else "fp32"]
+            keys = [k for k in ("mlp_i8_f64_adjoint", "adj_gemm_i8_f64", "adj_gemm_f64", "adj_gemm_f32") if k in tr]
+            n_adj, t_adj = (sum(tr[k][i] for k in keys) for i in (0, 1))
+            last_flops = sum(2.0 * rows * net["W"][-1].size for net in m["nets"])
+            digits = any("_i8" in k for k in keys)
+            if not digits:
+                peak = MI355X_PEAK["fp64" if prec == "fp64" else "fp32"]
+            elif "adj_gemm_f64" in keys:                        # the output layer
+                peak = round(back_flops / (last_flops / MI355X_PEAK["fp64"] + (back_flops - last_flops) / DIGIT_PEAK), 1)
+            else:
+                peak = DIGIT_PEAK
             achieved = back_flops / (t_adj * 1e-3) / 1e12 if t_adj > 0 else None
             out[f"{name}_{prec}"] = dict(
                 batch=B, ms_per_call=round(ms, 3), grads_per_s=round(B / (ms * 1e-3), 1),
-                backward_gemm=dict(kernel=key, launches=n_adj, total_us=round(t_adj * 1e3, 1),
+                backward_gemm=dict(kernel=" + ".join(keys), launches=n_adj, total_us=round(t_adj * 1e3, 1),
                                    work_flop=back_flops, achieved_tflops=None if achieved is None else round(achieved, 2),
                                    peak_tflops=peak, frac=None if achieved is None else round(achieved / peak, 4)),
                 kernels_us={k: round(t / n * 1e3, 2) for k, (n, t) in tr.items()})
