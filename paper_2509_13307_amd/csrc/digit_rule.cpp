@@ -42,56 +42,71 @@ static double bound_of(double mx) {
     return 128.0 * std::ldexp(std::ceil(256.0 * m) / 256.0, e);
 }
 
-int digit_row_minimum(const double* W, int units, int inputs, int64_t su, int64_t si) {
-    std::vector<double> faint(inputs, 0.0);               // sum over units of (w / rms of the unit)^2
-    double worst = 0.0;                                   // largest of the blocks' mean (B sqrt(n) / |w|)^2
-    std::vector<double> sq(units, 0.0);
-    for (int k0 = 0; k0 < inputs; k0 += BLOCK) {
-        const int n = std::min(BLOCK, inputs - k0);
-        double sum = 0.0;
-        int live = 0;
-        for (int u = 0; u < units; ++u) {
-            const double* w = W + u * su + k0 * si;
-            double mx = 0.0, ss = 0.0;
-            for (int k = 0; k < n; ++k) {
-                const double v = std::fabs(w[k * si]);
-                if (!std::isfinite(v)) return 0;
-                mx = std::max(mx, v);
-                ss += v * v;
+int digit_row_minimum(const double* W, int units, int inputs) {
+    std::vector<double> faint(inputs, 0.0);               // sum over units of (w / norm of the unit)^2
+    std::vector<double> worst((inputs + BLOCK - 1) / BLOCK, 0.0);   // per block: sum of (B sqrt(n) / |w|)^2
+    std::vector<int> live(worst.size(), 0);
+    int units_live = 0;
+    for (int u = 0; u < units; ++u) {
+        const double* w = W + (int64_t)u * inputs;
+        double total = 0.0;
+        for (int k0 = 0, b = 0; k0 < inputs; k0 += BLOCK, ++b) {
+            const int n = std::min(BLOCK, inputs - k0);
+            // four sums side by side: one would wait for itself at each weight
+            double mx4[4] = {}, ss4[4] = {};
+            for (int k = 0; k + 4 <= n; k += 4)
+                for (int e = 0; e < 4; ++e) {
+                    const double v = std::fabs(w[k0 + k + e]);
+                    mx4[e] = mx4[e] < v ? v : mx4[e];
+                    ss4[e] += v * v;
+                }
+            for (int k = n & ~3; k < n; ++k) {
+                mx4[0] = std::max(mx4[0], std::fabs(w[k0 + k]));
+                ss4[0] += w[k0 + k] * w[k0 + k];
             }
-            sq[u] += ss;
-            if (mx == 0.0) continue;                      // exact in digits
-            if (!(mx > 1e-140 && mx < 1e140) || mx * mx * n > 64.0 * ss) return 0;
+            const double mx = std::max(std::max(mx4[0], mx4[1]), std::max(mx4[2], mx4[3]));
+            const double ss = (ss4[0] + ss4[1]) + (ss4[2] + ss4[3]);
+            if (ss == 0.0 && mx == 0.0) continue;         // exact in digits
+            // (not finite: the sum is not)
+            if (!(ss < INFINITY) || !(mx > 1e-140 && mx < 1e140) || mx * mx * n > 64.0 * ss) return 0;
+            total += ss;
             const double tiny = std::sqrt(ss / n) / 32.0;
             int present = 0;
-            for (int k = 0; k < n; ++k) present += std::fabs(w[k * si]) >= tiny;
+            for (int k = k0; k < k0 + n; ++k) present += std::fabs(w[k]) >= tiny;
             if (2 * present < n) return 0;
             const double q = bound_of(mx);
-            sum += q * q * n / ss;
-            ++live;
+            worst[b] += q * q * n / ss;
+            ++live[b];
         }
-        if (live) worst = std::max(worst, sum / live);
+        if (total == 0.0) continue;
+        ++units_live;
+        const double per = 1.0 / total;
+        for (int k = 0; k < inputs; ++k) faint[k] += w[k] * w[k] * per;
     }
-    if (worst == 0.0) return 1;                           // no weights at all: exact zeros
-    int live = 0;
-    for (int u = 0; u < units; ++u) {
-        if (sq[u] == 0.0) continue;
-        ++live;
-        for (int k = 0; k < inputs; ++k) {
-            const double v = W[u * su + k * si];
-            faint[k] += v * v * inputs / sq[u];
-        }
-    }
+    if (units_live == 0) return 1;                        // no weights at all: exact zeros
+    double most = 0.0;
+    for (size_t b = 0; b < worst.size(); ++b)
+        if (live[b]) most = std::max(most, worst[b] / live[b]);
     std::sort(faint.begin(), faint.end());
     const int nf = std::max(1, inputs / 32);
     double low = 0.0;
-    for (int k = 0; k < nf; ++k) low += faint[k] / nf / live;
+    for (int k = 0; k < nf; ++k) low += faint[k] * inputs / nf / units_live;
     if (!(low > 0.0)) return 0;
-    const double f2 = worst / low;
+    const double f2 = most / low;
     // rows of which the largest entry is four times the rms should pass, at
     // the middle of the powers of two: f 1.5 4 / sqrt(inputs) <= limit, with some room
     if (f2 > 0.36 * std::min(inputs, BLOCK)) return 0;
     return (int)std::ceil(128.0 * 128.0 * f2 / (DG_ROW_LIMIT * DG_ROW_LIMIT));
+}
+
+// W^T [K x N] of W [N x K] into T, in squares that stay in cache.
+static const double* transposed(const double* W, int N, int K, std::vector<double>& T) {
+    if (T.size() < (size_t)N * K) T.resize((size_t)N * K);
+    for (int n0 = 0; n0 < N; n0 += 32)
+        for (int k0 = 0; k0 < K; k0 += 32)
+            for (int k = k0; k < std::min(K, k0 + 32); ++k)
+                for (int n = n0; n < std::min(N, n0 + 32); ++n) T[(size_t)k * N + n] = W[(size_t)n * K + k];
+    return T.data();
 }
 
 bool digit_shape(const std::vector<int>& dims) {
@@ -107,6 +122,7 @@ DigitPlan digit_plan(const ns_model_desc* D) {
     if (!D->nets || D->n_nets < 1) return p;
     p.forward = p.back = p.out = true;
     p.nets.resize(D->n_nets);
+    std::vector<double> turned;
     for (int i = 0; i < D->n_nets && p.forward; ++i) {
         const ns_net_desc& nd = D->nets[i];
         DigitPlan::Rows& r = p.nets[i];
@@ -122,11 +138,11 @@ DigitPlan digit_plan(const ns_model_desc* D) {
         for (int l = 1; l < nd.n_layers; ++l) {
             const int K = dims[l], N = dims[l + 1];
             const bool last = l == nd.n_layers - 1;
-            r.forward[l] = digit_row_minimum(nd.W[l], N, K, K, 1);
+            r.forward[l] = digit_row_minimum(nd.W[l], N, K);
             if (!r.forward[l]) return DigitPlan{};
             if (last && D->kind == NS_MODEL_SHEAR) p.out = false;
             if (last ? !p.out : !p.back) continue;
-            r.back[l] = digit_row_minimum(nd.W[l], K, N, 1, K);
+            r.back[l] = digit_row_minimum(transposed(nd.W[l], N, K, turned), K, N);
             if (!r.back[l]) (last ? p.out : p.back) = false;
         }
     }

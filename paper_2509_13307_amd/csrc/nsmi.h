@@ -374,9 +374,9 @@ bool emulator_backward_digits(ns_model* m, const int* nets, int G, int64_t B, co
 // conversions and activations the same.
 bool digit_shape(const std::vector<int>& dims);
 // The least sum of squared leading digits of an input row that runs on digits
-// against the units W [units x inputs] (element strides su, si), 0 if the
-// layer does not run on digits (digit_rule.cpp).
-int digit_row_minimum(const double* W, int units, int inputs, int64_t su, int64_t si);
+// against the units W [units x inputs], 0 if the layer does not run on digits
+// (digit_rule.cpp).
+int digit_row_minimum(const double* W, int units, int inputs);
 // Which layers of a model run on digits.  One answer for all its networks,
 // because they are launched as one group, whose kernels read every network's
 // digit tiles.  The adjoint's output layer of shear models stays on FP64
