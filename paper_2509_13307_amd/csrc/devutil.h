@@ -55,13 +55,13 @@ __device__ __forceinline__ double exp2_scaled(double x, double c_hi, double c_lo
     return fma(q, f, 1.0);
 }
 
-// e^x (FP64) as 2^n p with p in [0.7, 1.42], in half the library's
-// instructions: x = n ln 2 + r, r = rh - rl with rh exact,
-// e^r = 1 + rh + (r^2 q(r) - rl) with q of degree 9 interpolating at the
-// Chebyshev nodes of |r| <= ln(2)/2 (error 2e-17), what 1 + rh leaves over added
-// to the small terms.  Error against 80-bit values, in 2^-53: rms 0.438, at
+// e^x (FP64) as 2^n p with p in [0.7, 1.42]: x = n ln 2 + r, r = rh - rl with
+// rh exact, e^r = 1 + rh + (r^2 q(r) - rl) with q of degree 9 interpolating at
+// the Chebyshev nodes of |r| <= ln(2)/2 (error 2e-17), what 1 + rh leaves over
+// added to the small terms.  Error against 80-bit values, in 2^-53: rms 0.438, at
 // most 1.09 (the library's 0.446 and 1.22; as 2^(x log2 e) in one polynomial
-// 0.452 and 1.42).  |x| < 2^31.
+// 0.452 and 1.42).  |x| < 2^31.  exp_of takes 34 vector instructions, the
+// library's exp 41.
 __device__ __forceinline__ double exp_parts(double x, int& n) {
     const double t = fma(x, 0x1.71547652b82fep+0, 0x1.8p52);
     const double m = t - 0x1.8p52;
@@ -88,11 +88,12 @@ __device__ __forceinline__ double exp_of(double x) {
     return ldexp(p, n);
 }
 
-// 1 / (1 + exp(-u)).  FP64: without the library's exp and division, which are
-// what bounds the layers' epilogues; u is held to [-700, 700] (outside, the
-// sigmoid is 0 or 1 to 1e-304), a NaN stays one.  Error for normal arguments of
-// scale 1 (0.1 to 30), in 2^-53: rms 0.665 (0.585 to 0.739), at most 2.07 (2.42);
-// with the library's exp and division 0.670 (0.589 to 0.740), 2.14 (2.42).
+// 1 / (1 + exp(-u)).  FP64: in 40 vector instructions instead of 53 with the
+// library's exp and division, which are what bounds the layers' epilogues; u is
+// held to [-700, 700] (outside, the sigmoid is 0 or 1 to 1e-304), a NaN stays
+// one.  Error for normal arguments of scale 1 (0.1 to 30), in 2^-53: rms 0.665
+// (0.585 to 0.739), at most 2.07 (2.42); with the library's exp and division
+// 0.670 (0.589 to 0.740), 2.14 (2.42).
 template <class T> __device__ __forceinline__ T sigmoid(T u);
 template <> __device__ __forceinline__ double sigmoid<double>(double u) {
     u = u > 700.0 ? 700.0 : u;
@@ -111,7 +112,7 @@ template <> __device__ __forceinline__ float sigmoid<float>(float u) {
 }
 // 10^y (output transform of log10-emulated spectra)
 template <class T> __device__ __forceinline__ T exp10_of(T y);
-// FP64: 2^(y log2 10), 23 instead of 57 instructions, and without the rounding
+// FP64: 2^(y log2 10), 28 instead of 42 vector instructions, and without the rounding
 // of y ln 10; beyond the range of a double it overflows and underflows alike
 template <> __device__ __forceinline__ double exp10_of<double>(double y) {
     y = y > 400.0 ? 400.0 : y;

@@ -3,22 +3,26 @@
 //
 // Digits hold every entry of a row (or of a unit's weights) to one absolute
 // step, 2^-55 of a bound B just above the block's largest entry (the next power
-// of two for rows; for weights 1/127 to 1/128 above the entry itself), and the
+// of two for rows; for weights at most 1/60 above the entry itself), and the
 // dropped digit products are of that size too.  The error of one output is so
 // proportional to the product of two bounds, while an FP64 chain's is
 // proportional to the products present, |x w| in the 2-norm.  With
 //   f = rms over units of (B sqrt(inputs) / |w|)
 //       / rms weight of the faintest inputs (units scaled to rms 1)
 // (the faintest thirty-second of the inputs: a row whose large entries all meet
-// those) and s = f B / |x| for the row, digits have 0.28 to 0.37 s of the error
-// of an FP64 chain over 256 to 512 inputs: measured against extended precision
-// over normal, rectified, exponential, log-normal, Student-t, bump-shaped and
-// decaying rows (sparse ones up to 0.5 s) against normal, uniform, Laplace and
-// Student-t weights.  Rows with s above DG_ROW_LIMIT = 2.75 therefore take FP64
-// products, row by row, in the kernels (|x|^2 from the sum of squares of the
-// leading digits, whose unit is B / 128).  A normal row of 512 has s of 0.6 to
-// 1.3 against normal weights; of 50 000 activation rows of the emulators none
-// reached 2.4.
+// those) and s = f B 0.8 sqrt(inputs) / sum |x| for the row (for normal entries
+// f B / |x|; the sum, because rows of few or a few large entries also make FP64
+// sums of few roundings), digits' error is up to 0.37 s of that of an FP64 chain
+// over 256 to 512 inputs and 0.4 s over 128, on average 0.3 s: measured against
+// extended precision over normal, rectified, exponential, log-normal,
+// Student-t, sparse, bump-shaped and decaying rows, rows of 1 to 48 entries and
+// of one entry 6 to 40 times the others, against normal, uniform, Laplace and
+// Student-t weights (with |x| in the place of the sum, rows of two entries reach
+// hundreds).  Rows with s above DG_ROW_LIMIT = 2.5 therefore take FP64 products,
+// row by row, in the kernels (sum |x| from the leading digits' magnitudes, whose
+// unit is B / 128).  A normal row of 512 has s of 0.6 to 1.3 against normal
+// weights; of 60 000 rows of activations and of hidden and CMB output deltas of
+// the emulators none exceeded 2.1, of the shear's output deltas 95% did.
 //
 // A layer whose weights leave most rows to FP64, or whose units hold mostly
 // zeros (an error bound by the largest entries would then exceed an FP64
@@ -32,7 +36,7 @@
 namespace nsmi {
 
 constexpr int BLOCK = 512;              // inputs that share a scale (DG_K)
-constexpr double DG_ROW_LIMIT = 2.75;
+constexpr double DG_ROW_LIMIT = 2.5;
 
 // Bound of a block of weights of which mx is the largest magnitude: 128 times
 // the step of the leading digit, as the weights' kernel chooses it.
@@ -43,6 +47,7 @@ static double bound_of(double mx) {
 }
 
 int digit_row_minimum(const double* W, int units, int inputs) {
+    if (inputs < 128) return 0;                           // short sums: FP64's errors are the smaller (up to 0.7 s)
     std::vector<double> faint(inputs, 0.0);               // sum over units of (w / norm of the unit)^2
     std::vector<double> worst((inputs + BLOCK - 1) / BLOCK, 0.0);   // per block: sum of (B sqrt(n) / |w|)^2
     std::vector<int> live(worst.size(), 0);
@@ -96,7 +101,7 @@ int digit_row_minimum(const double* W, int units, int inputs) {
     // rows of which the largest entry is four times the rms should pass, at
     // the middle of the powers of two: f 1.5 4 / sqrt(inputs) <= limit, with some room
     if (f2 > 0.36 * std::min(inputs, BLOCK)) return 0;
-    return (int)std::ceil(128.0 * 128.0 * f2 / (DG_ROW_LIMIT * DG_ROW_LIMIT));
+    return (int)std::ceil(128.0 * 0.8 * std::sqrt(f2 * inputs) / DG_ROW_LIMIT);
 }
 
 // W^T [K x N] of W [N x K] into T, in squares that stay in cache.

@@ -22,7 +22,7 @@
 // relative to its own size instead, so digits are the better of the two only
 // where a row's entries, and a unit's weights, are of similar size.  Both are
 // checked: the weights on the host (digit_rule.cpp), and every row where it is
-// converted, from the sum of squares of its leading digits; a row that fails,
+// converted, from the sum of its leading digits' magnitudes; a row that fails,
 // or holds infinities, NaN or values beyond 2^(+-900), takes FP64 products in
 // the same kernels (fp64_rows below).  On rows that pass, the error against
 // extended precision is below an FP64 chain's (a third of it for normal draws).
@@ -71,18 +71,16 @@ __device__ __forceinline__ DigitScale digit_scale(int max_hi) {
     return s;
 }
 // Whether digits serve a row of one block: its largest magnitude's high word,
-// and the sum of squares of its leading digits against the layer's minimum.
-__device__ __forceinline__ bool digit_row(int max_hi, int squares, int minimum) {
-    return squares >= minimum || max_hi == 0;
-}
+// and the sum of its leading digits' magnitudes against the layer's minimum.
+__device__ __forceinline__ bool digit_row(int max_hi, int sum, int minimum) { return sum >= minimum || max_hi == 0; }
 // A row's factor, marked where no digits can hold it.
 __device__ __forceinline__ double row_factor(int max_hi) {
     const double back = digit_scale(max_hi).back;
     return back == 0.0 && max_hi != 0 ? DG_FP64 : back;
 }
-// The same over several blocks of K inputs: each block's squares, and its share
-// of the inputs, weigh with its factor's square.
-__device__ __forceinline__ bool digit_row(const double* factors, const int* squares, int stride, int K, int minimum) {
+// The same over several blocks of K inputs: the blocks' sums weigh with their
+// factors, and the factor that the whole is held against is their root mean square.
+__device__ __forceinline__ bool digit_row(const double* factors, const int* sums, int stride, int K, int minimum) {
     const int blocks = (K + DG_K - 1) / DG_K;
     double most = 0.0;
     bool held = true;
@@ -93,20 +91,20 @@ __device__ __forceinline__ bool digit_row(const double* factors, const int* squa
     }
     double have = 0.0, need = 0.0;
     for (int b = 0; b < blocks && most > 0.0; ++b) {
-        const double q = factors[b * stride] / most, q2 = q * q;
-        have += squares[b * stride] * q2;
-        need += min(DG_K, K - b * DG_K) * q2;
+        const double q = factors[b * stride] / most;
+        have += sums[b * stride] * q;
+        need += min(DG_K, K - b * DG_K) * q * q;
     }
-    return held && have * K >= minimum * need;
+    return held && have * have * K >= (double)minimum * minimum * need;
 }
 // The rows of a row block that digits do not serve (lane % 32, those that are
 // `in`), a bit each: marked by their factors.
 __device__ __forceinline__ uint32_t fp64_set(const double* factors, bool in, int lane) {
     return (uint32_t)__ballot(in && factors[lane & 31] < 0.0);
 }
-// Sum of squares of the four leading digits in a word, added to s.
-__device__ __forceinline__ int digit_squares(uint32_t d0, int s) {
-    return __builtin_amdgcn_sdot4((int)d0, (int)d0, s, false);
+// Magnitudes of the four leading digits in a word, added to s.
+__device__ __forceinline__ uint32_t digit_sum(uint32_t d0, uint32_t s) {
+    return __builtin_amdgcn_sad_u8(d0 ^ 0x80808080u, 0x80808080u, s);
 }
 
 // Seven balanced digits of x * to_int, least significant in byte 0.  The
@@ -247,8 +245,9 @@ struct PlaneRows {
                 x[q][s][0] = a.x; x[q][s][1] = a.y; x[q][s][2] = b.x; x[q][s][3] = b.y;
             }
     }
-    __device__ __forceinline__ void store(char* planes, double* back, int* squares, int kc, int wave, int lane) const {
-        int mx[4], sq[4];
+    __device__ __forceinline__ void store(char* planes, double* back, int* sums, int kc, int wave, int lane) const {
+        int mx[4];
+        uint32_t sq[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             mx[q] = 0;
@@ -268,7 +267,7 @@ struct PlaneRows {
                 if (256 * s + 4 * lane >= kc) continue;
                 uint32_t d[DG_N];
                 pack4(x[q][s], sc.to_int, d);
-                sq[q] = digit_squares(d[0], sq[q]);
+                sq[q] = digit_sum(d[0], sq[q]);
                 char* dst = planes + (4 * wave + q) * DG_LDS + 256 * s + 4 * lane;
 #pragma unroll
                 for (int i = 0; i < DG_N; ++i) *reinterpret_cast<uint32_t*>(dst + i * DG_PLANE) = d[i];
@@ -276,10 +275,10 @@ struct PlaneRows {
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int sum = wave_total(sq[q]);
+            const int sum = wave_total((int)sq[q]);
             if (lane == 0) {
                 back[4 * wave + q] = row_factor(mx[q]);
-                squares[4 * wave + q] = sum;
+                sums[4 * wave + q] = sum;
             }
         }
     }
@@ -309,7 +308,7 @@ __global__ __launch_bounds__(MULTI ? 64 * DR_WAVES : 256) void digit_rows_kernel
     extern __shared__ __attribute__((aligned(16))) char dr_lds[];
     const int blocks = MULTI ? (K + DG_K - 1) / DG_K : 1;
     double* factors = reinterpret_cast<double*>(dr_lds);
-    int* squares = reinterpret_cast<int*>(factors + blocks);
+    int* sums = reinterpret_cast<int*>(factors + blocks);
     for (int blk = MULTI ? wave : 0; blk < blocks; blk += DR_WAVES) {
         const int k = blk * DG_K + lane * 4;             // and + 256
         const double* src = P.A[g] + (row0 + r) * lda + k;
@@ -327,30 +326,30 @@ __global__ __launch_bounds__(MULTI ? 64 * DR_WAVES : 256) void digit_rows_kernel
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) h = max(h, __shfl_xor(h, o, 64));
         const DigitScale sc = digit_scale(h);
-        int sq = 0;
+        uint32_t sq = 0;
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             const int ks = k + 256 * s;
             if (ks >= K) break;
             uint32_t d[DG_N];
             pack4(x[s], sc.to_int, d);
-            sq = digit_squares(d[0], sq);
+            sq = digit_sum(d[0], sq);
             char* t = P.tiles[g] + digit_offset(r, ks, K);
 #pragma unroll
             for (int i = 0; i < DG_N; ++i) *reinterpret_cast<uint32_t*>(t + i * 1024) = d[i];
         }
-        sq = wave_total(sq);
+        const int sum = wave_total((int)sq);
         if (lane > 0) continue;
         if (MULTI) {
             factors[blk] = row_factor(h);
-            squares[blk] = sq;
+            sums[blk] = sum;
         } else {
-            P.back[g][r] = digit_row(h, sq, P.minimum[g]) ? row_factor(h) : DG_FP64;
+            P.back[g][r] = digit_row(h, sum, P.minimum[g]) ? row_factor(h) : DG_FP64;
         }
     }
     if (!MULTI) return;
     __syncthreads();
-    const bool served = digit_row(factors, squares, 1, K, P.minimum[g]);
+    const bool served = digit_row(factors, sums, 1, K, P.minimum[g]);
     for (int b = threadIdx.x; b < blocks; b += 64 * DR_WAVES) P.back[g][b * m32 + r] = served ? factors[b] : DG_FP64;
 }
 

@@ -44,12 +44,12 @@ constexpr int DM_STEP = DG_N * 64;                  // 16-byte units of one K st
 // offset from one base register (behind the planes each address would take a
 // register of its own)
 constexpr int DM_MAX = 4 * DM_H * 8;                // after the layer parameters [4][512]: row maxima [2][32]
-constexpr int DM_SQ = DM_MAX + 2 * DG_ROWS * 4;     // rows' sums of squared leading digits [2][32]
-constexpr int DM_BACK = DM_SQ + 2 * DG_ROWS * 4;    // row factors [32]
+constexpr int DM_SUM = DM_MAX + 2 * DG_ROWS * 4;     // rows' sums of leading digits [2][32]
+constexpr int DM_BACK = DM_SUM + 2 * DG_ROWS * 4;    // row factors [32]
 constexpr int DM_ZROW = DM_BACK + DG_ROWS * 8;      // rows' redshift nodes [32]
 constexpr int DM_PLANES = DM_ZROW + DG_ROWS * 4;    // digit planes
 constexpr int DM_ROWS64 = DM_PLANES + DG_N * DG_PLANE;   // four rows of values [4][512]
-constexpr int DM_MAXBLOCKS = 4 * DM_H * 8 / (DG_ROWS * 12);   // blocks whose factors and squares fit there
+constexpr int DM_MAXBLOCKS = 4 * DM_H * 8 / (DG_ROWS * 12);   // blocks whose factors and sums fit there
 constexpr int DM_LDS_BYTES = DM_ROWS64 + 4 * DM_H * 8;
 
 struct DigitLayer {
@@ -96,7 +96,7 @@ struct DigitWave {
 
     __device__ __forceinline__ double* prm(int i) const { return reinterpret_cast<double*>(lds) + i * DM_H; }
     __device__ __forceinline__ int* rmax(int p) const { return reinterpret_cast<int*>(lds + DM_MAX) + p * DG_ROWS; }
-    __device__ __forceinline__ int* rsq(int p) const { return reinterpret_cast<int*>(lds + DM_SQ) + p * DG_ROWS; }
+    __device__ __forceinline__ int* rsum(int p) const { return reinterpret_cast<int*>(lds + DM_SUM) + p * DG_ROWS; }
     __device__ __forceinline__ double* rows64() const { return reinterpret_cast<double*>(lds + DM_ROWS64); }
     __device__ __forceinline__ double* rback() const { return reinterpret_cast<double*>(lds + DM_BACK); }
     // units 8 q + 256 t (+ 0..3) of the lane's row in such a block: a uniform base, the lane's offset and an immediate
@@ -218,10 +218,10 @@ struct DigitWave {
         back = sc.back;
         if (wave == 0 && lane < 32) {
             rmax(p ^ 1)[row] = 0;
-            rsq(p ^ 1)[row] = 0;
+            rsum(p ^ 1)[row] = 0;
             rback()[row] = back;
         }
-        int sq = 0;
+        uint32_t sq = 0;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -229,17 +229,17 @@ struct DigitWave {
                 const double v[4] = {h[t][4 * q], h[t][4 * q + 1], h[t][4 * q + 2], h[t][4 * q + 3]};
                 uint32_t d[DG_N];
                 pack4(v, sc.to_int, d);
-                sq = digit_squares(d[0], sq);
+                sq = digit_sum(d[0], sq);
                 char* dst = lds + DM_PLANES + row * DG_LDS + (wave + 8 * t) * 32 + u0 + 8 * q;
 #pragma unroll
                 for (int i = 0; i < DG_N; ++i) *reinterpret_cast<uint32_t*>(dst + i * DG_PLANE) = d[i];
                 __builtin_amdgcn_sched_barrier(0);
             }
         sq += __shfl_xor(sq, 32, 64);
-        if (lane < 32) atomicAdd(&rsq(p)[row], sq);
+        if (lane < 32) atomicAdd(&rsum(p)[row], (int)sq);
         stage();
         __syncthreads();
-        odd = (uint32_t)__ballot(counts && !digit_row(rmax(p)[row], rsq(p)[row], minimum));
+        odd = (uint32_t)__ballot(counts && !digit_row(rmax(p)[row], rsum(p)[row], minimum));
         load_x();
     }
 };
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(512) void mlp_i8_kernel(const double* __restrict__ 
     S.prm(0)[tid] = N.b1[tid];
     S.prm(1)[tid] = N.be1[tid];
     S.prm(2)[tid] = N.ga1[tid];
-    if (tid < 2 * DG_ROWS) S.rmax(0)[tid] = S.rsq(0)[tid] = 0;
+    if (tid < 2 * DG_ROWS) S.rmax(0)[tid] = S.rsum(0)[tid] = 0;
     int* zrow = reinterpret_cast<int*>(lds + DM_ZROW);
     if (tid < DG_ROWS) zrow[tid] = A.mu_rows > 1 ? (int)((m0 + tid) % A.mu_rows) * A.N_out : 0;
     double xv[NI];
@@ -459,7 +459,7 @@ __global__ __launch_bounds__(512) void mlp_i8_back_kernel(int64_t rows, int n_pa
     const int wave = S.wave, lane = S.lane;
     const int64_t grow = m0 + S.row;
     const bool valid = grow < rows;
-    if (tid < 2 * DG_ROWS) S.rmax(0)[tid] = S.rsq(0)[tid] = 0;
+    if (tid < 2 * DG_ROWS) S.rmax(0)[tid] = S.rsum(0)[tid] = 0;
 
     double h[2][16];
     // delta_l W_l, times f'(t) of the layer below (rows past the end: t = 0)
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(512) void mlp_i8_back_kernel(int64_t rows, int n_pa
         S.prm(2)[tid] = B.gamma[tid];
     }
     const i32x4_t* wt = N.out.W + (int64_t)wave * KB * DM_STEP + lane;
-    int* squares = reinterpret_cast<int*>(S.rows64() + DM_MAXBLOCKS * DG_ROWS);
+    int* sums = reinterpret_cast<int*>(S.rows64() + DM_MAXBLOCKS * DG_ROWS);
     S.load_w(N.out.W ? wt : N.hid[A.n_hidden - 1].W + (int64_t)wave * 16 * DM_STEP + lane);
     if (!N.out.W) __syncthreads();                       // the row maxima are cleared
     for (int k0 = 0; k0 < n_pad && N.out.W; k0 += DG_K) {
@@ -500,7 +500,7 @@ __global__ __launch_bounds__(512) void mlp_i8_back_kernel(int64_t rows, int n_pa
         R.load(N.delta, n_pad, m0, rows, k0, kc, wave, lane);
         if (k0) __syncthreads();                         // every wave past its reads of the planes
         double* factors = S.rows64() + k0 / DG_K * DG_ROWS;
-        R.store(lds + DM_PLANES, factors, squares + k0 / DG_K * DG_ROWS, kc, wave, lane);
+        R.store(lds + DM_PLANES, factors, sums + k0 / DG_K * DG_ROWS, kc, wave, lane);
         S.prm(3)[tid] = N.out.back[(int64_t)(k0 / DG_K) * DM_H + tid];
         __syncthreads();
         S.back = factors[S.row];
@@ -533,8 +533,8 @@ __global__ __launch_bounds__(512) void mlp_i8_back_kernel(int64_t rows, int n_pa
     // rows that digits do not serve, all their blocks
     if (N.out.W) {
         const double* factors = S.rows64() + S.row;
-        const bool served = n_pad > DG_K ? digit_row(factors, squares + S.row, DG_ROWS, n_pad, N.out.minimum)
-                                         : factors[0] == 0.0 || (factors[0] > 0.0 && squares[S.row] >= N.out.minimum);
+        const bool served = n_pad > DG_K ? digit_row(factors, sums + S.row, DG_ROWS, n_pad, N.out.minimum)
+                                         : factors[0] == 0.0 || (factors[0] > 0.0 && sums[S.row] >= N.out.minimum);
         S.odd = (uint32_t)__ballot(valid && !served);
         for (int k0 = 0; k0 < n_pad && __builtin_expect(S.odd != 0, 0); k0 += DG_K)
             S.products64([&](int r, double* place) {

@@ -87,7 +87,7 @@ struct Layer {
     DevBuf WT64, WT32;                       // W^T [n_in x n_pad], zero padded (adjoint)
     DevBuf Wd, wback, WTd, wtback;           // base-256 digit tiles of W and W^T and their units' factors
                                              // (where the model's DigitPlan has the layer on digits; gemm_i8.h)
-    int dmin = 0, dtmin = 0;                 // ... and their input rows' least sum of squared leading digits
+    int dmin = 0, dtmin = 0;                 // ... and their input rows' least sum of leading digits
 };
 
 struct Net {
@@ -373,7 +373,7 @@ bool emulator_backward_digits(ns_model* m, const int* nets, int G, int64_t B, co
 // 128 inputs a tile's digit products take a quarter of the time, its 1024
 // conversions and activations the same.
 bool digit_shape(const std::vector<int>& dims);
-// The least sum of squared leading digits of an input row that runs on digits
+// The least sum of leading digits of an input row that runs on digits
 // against the units W [units x inputs], 0 if the layer does not run on digits
 // (digit_rule.cpp).
 int digit_row_minimum(const double* W, int units, int inputs);

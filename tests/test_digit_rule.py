@@ -27,7 +27,7 @@ def admitted():
     return ask
 
 
-def four(hidden=(512, 512), n_ell=70):
+def four(hidden=(512, 512), n_ell=140):
     m = W.cmb_block_structure(n_ell=n_ell, hidden=hidden)
     m.update(data=np.ones(4 * n_ell), cov_blocks=np.tile(np.eye(3), (n_ell, 1, 1)), sigma_pp=np.ones(n_ell))
     return m
@@ -39,6 +39,7 @@ FORWARD, HIDDEN_ADJOINT, OUTPUT_ADJOINT = 1, 2, 4
 def test_even_networks_are_admitted(admitted):
     assert admitted(four()) == FORWARD | HIDDEN_ADJOINT | OUTPUT_ADJOINT
     assert admitted(four(hidden=(256, 320))) == FORWARD | HIDDEN_ADJOINT | OUTPUT_ADJOINT
+    assert admitted(four(n_ell=70)) == FORWARD | HIDDEN_ADJOINT     # sums of fewer than 128 products
     assert not admitted(four(hidden=(512, 128)))
 
 
