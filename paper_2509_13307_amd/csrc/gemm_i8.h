@@ -97,11 +97,6 @@ __device__ __forceinline__ bool digit_row(const double* factors, const int* sums
     }
     return held && have * have * K >= (double)minimum * minimum * need;
 }
-// The rows of a row block that digits do not serve (lane % 32, those that are
-// `in`), a bit each: marked by their factors.
-__device__ __forceinline__ uint32_t fp64_set(const double* factors, bool in, int lane) {
-    return (uint32_t)__ballot(in && factors[lane & 31] < 0.0);
-}
 // Magnitudes of the four leading digits in a word, added to s.
 __device__ __forceinline__ uint32_t digit_sum(uint32_t d0, uint32_t s) {
     return __builtin_amdgcn_sad_u8(d0 ^ 0x80808080u, 0x80808080u, s);
@@ -403,7 +398,7 @@ __device__ __forceinline__ void next_rows(uint32_t& rem, int (&r)[4]) {
 // are added in order (tpw <= GI_TPW).  A, W: digit fragments of the rows and of
 // the units; Al, Wl: their factors [block][m32 or N rounded up to 32].  Rows
 // The launch takes the rows of a part, from row0 on (A and Al are the part's).  Rows
-// that digits do not serve (fp64_set) are left out and formed at the end, from
+// that digits do not serve (factor DG_FP64) are left out and formed at the end, from
 // A64 (row stride lda) and the weights Wk, input by input (stride ldw,
 // `present` inputs): there nothing else holds registers, and a launch without
 // such rows does not fetch the code.
@@ -468,7 +463,7 @@ __global__ __launch_bounds__(512) void gemm_i8_kernel(DigitGroup<Epi> G, int64_t
     const i32x4_t* X = static_cast<const i32x4_t*>(G.A[g]) + ((int64_t)blockIdx.y * KB + wave) * (DG_N * 64) + lane;
     const i32x4_t* W = static_cast<const i32x4_t*>(G.W[g]) + ((int64_t)t0 * KB + wave) * (DG_N * 64) + lane;
     const int ec = tid & 31, er = tid >> 5;              // epilogue: column, rows er and er + 16
-    const uint32_t odd = fp64_set(xback, m0 + (lane & 31) < M, lane);
+    uint32_t odd = 0;                                    // the wave's epilogue rows with the factor DG_FP64
     double tot[MULTI ? GI_TPW : 1][2];
     int zr[2] = {0, 0};
     if (const int per = epi.period()) {
@@ -555,7 +550,7 @@ __global__ __launch_bounds__(512) void gemm_i8_kernel(DigitGroup<Epi> G, int64_t
                     tot[t][i] = y;
                 }
                 const int64_t r = m0 + er + 16 * i;
-                if (last && r < M && c < N && !(odd >> (er + 16 * i) & 1)) epi.store(r, c, col, y, pre[i]);
+                if (last && r < M && c < N && xb[i] >= 0.0) epi.store(r, c, col, y, pre[i]);
             }
             buf ^= 1;
         };
@@ -569,8 +564,14 @@ __global__ __launch_bounds__(512) void gemm_i8_kernel(DigitGroup<Epi> G, int64_t
         } else {
             for (int t = 0; t < nt; ++t) tile(t, std::true_type{});
         }
+        if (k0 + DG_K >= K)                              // (asked at the start, the factors' loads took 0.8 us of a launch)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const unsigned long long marked = __ballot(m0 + er + 16 * i < M && xb[i] < 0.0);
+                odd |= (uint32_t)((marked & 1) | (marked >> 32 & 1) << 1) << (2 * wave + 16 * i);
+            }
     }
-    if (__builtin_expect(odd != 0, 0)) fp64_tiles(G, g, odd, m0, N, K, t0, nt, wave, 8, lane);
+    if (__builtin_expect(odd != 0, 0)) fp64_tiles(G, g, odd, m0, N, K, t0, nt, 0, 1, lane);
 }
 
 // The same layer for more tiles: a workgroup of WAVES waves copies its 32
@@ -597,7 +598,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_i8_wide_kernel(DigitGroup<Epi
     const i32x4_t* X = static_cast<const i32x4_t*>(G.A[g]) + (int64_t)blockIdx.y * KB * (DG_N * 64);
     const i32x4_t* W = static_cast<const i32x4_t*>(G.W[g]) + (int64_t)t0 * KB * (DG_N * 64) + lane;
     const double* xback = G.Al[g] + part + (lane >> 5) * 4;        // + 8 (r / 4) + r % 4
-    const uint32_t odd = fp64_set(G.Al[g] + part, m0 + (lane & 31) < M, lane);
+    const uint32_t odd = (uint32_t)__ballot(m0 + (lane & 31) < M && G.Al[g][part + (lane & 31)] < 0.0);   // DG_FP64
     const char* xa = lds + lane * 16;
     int* zrow = reinterpret_cast<int*>(lds + GW_ZR);
     const int per = epi.period();
