@@ -21,7 +21,9 @@
 // (the older of two waves on a SIMD goes first by itself, so that one's
 // activations run under the other's products).  The FP64 MFMA layers that this
 // replaced took 1 380 us (50 TFLOP/s), and the adjoint of 32 768 rows of one
-// 8-512^4-420 network 1 460 us against 990 us now.
+// 8-512^4-420 network 1 460 us against 1 070 us now (713 us here for the hidden
+// layers; its output layer's rows mostly fail the check and stay on FP64
+// products, 353 us).
 //
 // A layer's rows that digits do not serve (gemm_i8.h) take FP64 products: the
 // workgroup forms their next layer from the values themselves, four rows at a
