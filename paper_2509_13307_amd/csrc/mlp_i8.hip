@@ -241,7 +241,8 @@ struct DigitWave {
         if (lane < 32) atomicAdd(&rsum(p)[row], (int)sq);
         stage();
         __syncthreads();
-        odd = (uint32_t)__ballot(counts && !digit_row(rmax(p)[row], rsum(p)[row], minimum));
+        // (a row that no digits can hold by its factor: its leading digits may be anything)
+        odd = (uint32_t)__ballot(counts && (back == 0.0 ? rmax(p)[row] != 0 : rsum(p)[row] < minimum));
         load_x();
     }
 };

@@ -202,3 +202,23 @@ def test_infinite_and_huge_rows(B):
     print(f"  max error {err.max():.2e}", flush=True)
     assert err.max() <= 1e-11
     g.close()
+
+
+@pytest.mark.parametrize("B", [40, 4700])
+@pytest.mark.parametrize("bits", [0x7ff8000000000000, 0x7ff800007f7f7f7f, 0x7fffffffffffffff, 0x7ff80000007fffff])
+def test_nan_rows_of_any_payload(B, bits):
+    """A NaN is a NaN in every output and in the gradient, whatever its low bits
+    read as digits, and the rows beside it are what they are without it."""
+    print(f"case digit rows, NaN {bits:x} B={B}", flush=True)
+    m, _ = pair((512, 512))
+    th = torch.tensor(W.prior_draws(m, B, tag=57), device=DEV)
+    bad = th.clone()
+    bad.view(torch.int64)[[3, 20, B - 1], 2] = bits
+    rest = torch.ones(B, dtype=torch.bool, device=DEV)
+    rest[[3, 20, B - 1]] = False
+    g = Model(m)
+    y, (l, gr) = g.theory(th), g.loglike_grad(th)
+    yb, (lb, gb) = g.theory(bad), g.loglike_grad(bad)
+    assert torch.isnan(yb[~rest]).all() and torch.isnan(lb[~rest]).all() and torch.isnan(gb[~rest]).all()
+    assert torch.equal(yb[rest], y[rest]) and torch.equal(lb[rest], l[rest]) and torch.equal(gb[rest], gr[rest])
+    g.close()
